@@ -7,21 +7,20 @@
 // is column j and block b's weight rows (the paper's C_in x C_out orientation)
 // are the 64 columns perm[64 b .. 64 b + 63] of W, a 64 x N matrix W_b.
 //
-//  * Channel energies e_j = sum_n W[n][j]^2 in fp64, one workgroup per 64
+//  * Channel energies e_j = sum_n W[n][j]^2 in fp64, one workgroup per 16
 //    columns with a fixed reduction order (deterministic, so exactly equal
 //    columns get exactly equal energies).
 //  * Zigzag order: the descending rank of e_j (ties to the lower index) by
-//    counting, one thread per channel, then the snake deal over the blocks.
+//    counting, then the snake deal over the blocks.
 //  * U_b: the left singular vectors of W_b are the eigenvectors of the Gram
-//    matrix G_b = W_b W_b^T, with sigma_i^2 its eigenvalues.  G_b is formed in
-//    fp64 (exact products of fp16 values) in LDS, and diagonalized by the
-//    cyclic Jacobi method in fp64: each sweep visits all 2016 index pairs in
-//    63 steps of 32 disjoint pairs (round-robin order), the rotations of a
-//    step applied together as a column pass over G and V and a row pass over
-//    G; sweeps stop when one applies no rotation (at most 40).  Eigenpairs are ordered by
-//    descending eigenvalue (ties to the lower index) and each vector's sign
-//    is fixed so that its entry of largest magnitude (the first on ties) is
-//    positive.  One workgroup per block.
+//    matrix G_b = W_b W_b^T, with sigma_i^2 its eigenvalues.  G_b is formed on
+//    the fp64 matrix cores (exact products of fp16 values) and diagonalized by
+//    the cyclic Jacobi method in fp64: the 2016 index pairs in 63 steps of 32
+//    disjoint pairs (round-robin order), the 32 rotations of a step applied
+//    together, until 63 steps in a row (every pair) apply none (at most 40
+//    sweeps).  Eigenpairs are ordered by descending eigenvalue (ties to the
+//    lower index) and each vector's sign is fixed so that its entry of largest
+//    magnitude (the first on ties) is positive.  One workgroup per block.
 //  * R_b = U_b H_64 / 8 in fp64, rounded once to fp16 (round half to even)
 //    and stored column-major per block, the operand the online composite
 //    kernel reads.
@@ -40,7 +39,9 @@ namespace {
 
 constexpr int kB = 64;        // block size (the paper's)
 constexpr int kLd = kB + 1;   // padded LDS row of the 64 x 64 matrices
-constexpr int kMaxSweeps = 40;
+constexpr int kMaxSteps = 40 * 63;
+
+typedef double v4d __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double h2d(uint16_t h) {
   return static_cast<double>(static_cast<float>(__builtin_bit_cast(_Float16, h)));
@@ -74,207 +75,328 @@ __device__ __forceinline__ uint16_t f64_to_f16_rne(double x) {
   return sign | static_cast<uint16_t>(r);
 }
 
-// e[j] = sum_n W[n][j]^2: 64 columns per workgroup (one per lane), 16 waves
-// over the rows (wave w takes rows w, w + 16, ...), waves summed in order.
+// e[j] = sum_n W[n][j]^2: 16 columns per workgroup, 64 threads per column
+// (thread g takes rows g, g + 64, ...), their sums added in order.  Bound by
+// the one read of W once the columns are spread over the chip (64 columns per
+// workgroup left 7/8 of it idle: 2560 x 2048 148 us, now 10).
 __global__ __launch_bounds__(1024) void energy_kernel(const uint16_t* __restrict__ W, int64_t N, int64_t K,
                                                       int64_t ldw, double* __restrict__ e) {
-  __shared__ double part[16][64];
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t col = static_cast<int64_t>(blockIdx.x) * 64 + lane;
+  __shared__ double part[64][16];
+  const int c = threadIdx.x & 15, g = threadIdx.x >> 4;
+  const int64_t col = static_cast<int64_t>(blockIdx.x) * 16 + c;
   const bool ok = col < K;
   const uint16_t* wc = W + (ok ? col : 0);
   double acc = 0.0;
-  int64_t n = wv;
-  for (; n + 48 < N; n += 64) {
-    const double a0 = h2d(wc[n * ldw]), a1 = h2d(wc[(n + 16) * ldw]);
-    const double a2 = h2d(wc[(n + 32) * ldw]), a3 = h2d(wc[(n + 48) * ldw]);
-    acc = fma(a0, a0, acc);
-    acc = fma(a1, a1, acc);
-    acc = fma(a2, a2, acc);
-    acc = fma(a3, a3, acc);
+  int64_t n = g;
+  for (; n + 7 * 64 < N; n += 8 * 64) {
+    uint16_t w[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) w[u] = wc[(n + 64 * u) * ldw];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc = fma(h2d(w[u]), h2d(w[u]), acc);
   }
-  for (; n < N; n += 16) {
+  for (; n < N; n += 64) {
     const double a = h2d(wc[n * ldw]);
     acc = fma(a, a, acc);
   }
-  part[wv][lane] = acc;
+  part[g][c] = acc;
   __syncthreads();
-  if (wv == 0 && ok) {
+  if (threadIdx.x < 16 && ok) {
     double s = 0.0;
-    for (int w = 0; w < 16; ++w) s += part[w][lane];
+    for (int w = 0; w < 64; ++w) s += part[w][c];
     e[col] = s;
   }
 }
 
-// perm from energies: thread j counts the channels ranked before it
-// (larger energy, or equal energy and lower index), then deals rank i to
-// round i / nb and block (round even ? i % nb : nb - 1 - i % nb), slot round.
-__global__ __launch_bounds__(256) void zigzag_kernel(const double* __restrict__ e, int K, int nb,
-                                                     int32_t* __restrict__ perm) {
+// perm from energies: 64 channels per workgroup; wave w counts the channels of
+// its sixteenth of every 2048 that rank before channel j (larger energy, or
+// equal energy and lower index); rank i is dealt to round i / nb and block
+// (round even ? i % nb : nb - 1 - i % nb), slot round.
+__global__ __launch_bounds__(1024) void zigzag_kernel(const double* __restrict__ e, int K, int nb,
+                                                      int32_t* __restrict__ perm) {
   __shared__ double chunk[2048];
-  const int j = blockIdx.x * 256 + threadIdx.x;
+  __shared__ int part[16][64];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int j = blockIdx.x * 64 + lane;
   const double ej = j < K ? e[j] : 0.0;
   int rank = 0;
   for (int base = 0; base < K; base += 2048) {
     const int len = K - base < 2048 ? K - base : 2048;
     __syncthreads();
-    for (int i = threadIdx.x; i < len; i += 256) chunk[i] = e[base + i];
+    for (int i = threadIdx.x; i < len; i += 1024) chunk[i] = e[base + i];
     __syncthreads();
-    for (int i = 0; i < len; ++i) {
-      const double x = chunk[i];
-      rank += (x > ej || (x == ej && base + i < j)) ? 1 : 0;
-    }
+    // (Every channel before this workgroup's 64 wins a tie, every one after loses it.)
+    const int i0 = wv * 128, i1 = len < i0 + 128 ? len : i0 + 128;
+    const int lo = min(max(static_cast<int>(blockIdx.x) * 64 - base, i0), i1);
+    const int hi = min(max(static_cast<int>(blockIdx.x) * 64 + 64 - base, i0), i1);
+#pragma unroll 8
+    for (int i = i0; i < lo; ++i) rank += chunk[i] >= ej ? 1 : 0;
+    for (int i = lo; i < hi; ++i) rank += (chunk[i] > ej || (chunk[i] == ej && base + i < j)) ? 1 : 0;
+#pragma unroll 8
+    for (int i = hi; i < i1; ++i) rank += chunk[i] > ej ? 1 : 0;
   }
-  if (j >= K) return;
+  part[wv][lane] = rank;
+  __syncthreads();
+  if (wv != 0 || j >= K) return;
+  rank = 0;
+  for (int w = 0; w < 16; ++w) rank += part[w][lane];
   const int c = K / nb;
   const int r = rank / nb, p = rank % nb;
   const int b = (r & 1) ? nb - 1 - p : p;
   perm[b * c + r] = j;
 }
 
-// Pair m of step k of the round-robin order over 64 indices: (k, 63) for
-// m = 0, ((k + m) mod 63, (k - m) mod 63) otherwise; every unordered pair
-// occurs in exactly one of the 63 steps.
-__device__ __forceinline__ void rr_pair(int k, int m, int* p, int* q) {
-  int a, b;
-  if (m == 0) {
-    a = k;
-    b = 63;
-  } else {
-    a = (k + m) % 63;
-    b = (k - m + 63) % 63;
+// G_b = W_b W_b^T in fp64 on v_mfma_f64_16x16x4 (lane l holds row k = l / 16 of
+// W_b^T, column l % 16, for either operand; element i of the result is row
+// 4 i + l / 16, column l % 16).  The ten 16 x 16 tiles on and above the
+// diagonal go to six workgroups, each with at most two groups of 16 columns to
+// gather: (0,0)(0,1), (1,1)(1,2), (2,2)(2,3), (3,3)(3,0), (0,2), (1,3).  Its 8
+// waves take four rows in turn each; their sums are added in order.  Bound by
+// the gather (2-byte loads of permuted columns).
+__global__ __launch_bounds__(512) void gram_kernel(const uint16_t* __restrict__ W, int64_t N, int64_t K, int64_t ldw,
+                                                   const int32_t* __restrict__ perm, double* __restrict__ G) {
+  __shared__ double red[8][2][256];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b = blockIdx.x / 6, t = blockIdx.x % 6;
+  const int g0 = t < 4 ? t : t - 4, g1 = t < 4 ? (t + 1) & 3 : t - 2;
+  const bool two = t < 4;  // the diagonal tile (g0, g0) as well
+  auto column = [&](int g) {  // clamped: an out-of-range entry cannot address outside the row
+    const int32_t c = perm[b * kB + 16 * g + (lane & 15)];
+    return c < 0 ? 0 : (c >= K ? static_cast<int>(K - 1) : c);
+  };
+  const int kr = lane >> 4;
+  const uint16_t *w0 = W + column(g0), *w1 = W + column(g1);
+  v4d d = {0, 0, 0, 0}, x = {0, 0, 0, 0};
+  constexpr int UN = 8;
+  for (int64_t n0 = 4 * wv; n0 < N; n0 += 32 * UN) {
+    uint16_t a[UN], c[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int64_t n = n0 + 32 * u + kr, nc = n < N ? n : N - 1;  // clamped row; its value is replaced by 0
+      a[u] = w0[nc * ldw];
+      c[u] = w1[nc * ldw];
+      if (n >= N) a[u] = c[u] = 0;
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const double av = h2d(a[u]), cv = h2d(c[u]);
+      x = __builtin_amdgcn_mfma_f64_16x16x4f64(av, cv, x, 0, 0, 0);
+      if (two) d = __builtin_amdgcn_mfma_f64_16x16x4f64(av, av, d, 0, 0, 0);
+    }
   }
-  *p = a < b ? a : b;
-  *q = a < b ? b : a;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    red[wv][0][(4 * i + kr) * 16 + (lane & 15)] = x[i];
+    red[wv][1][(4 * i + kr) * 16 + (lane & 15)] = d[i];
+  }
+  __syncthreads();
+  const int which = threadIdx.x >> 8, el = threadIdx.x & 255;
+  if (which && !two) return;
+  double s = 0.0;
+  for (int w = 0; w < 8; ++w) s += red[w][which][el];
+  const int i = 16 * g0 + el / 16, j = 16 * (which ? g0 : g1) + el % 16;
+  double* g = G + static_cast<int64_t>(b) * kB * kB;
+  g[i * kB + j] = s;
+  if (!which) g[j * kB + i] = s;
 }
 
-// One workgroup (256 threads) per 64-channel block.
-__global__ __launch_bounds__(256) void block_eig_kernel(const uint16_t* __restrict__ W, int64_t N, int64_t K,
-                                                        int64_t ldw, const int32_t* __restrict__ perm,
-                                                        double* __restrict__ U, double* __restrict__ lam) {
-  __shared__ double X[64][64];    // a chunk of 64 rows of W_b^T (row n, column = block channel)
-  __shared__ double A[kB][kLd];   // G_b, then its Jacobi iterates
-  __shared__ double V[kB][kLd];   // accumulated rotations
-  __shared__ int cols[kB];
-  __shared__ int pp[32], pq[32];
-  __shared__ double pc[32], ps[32];
-  __shared__ int nrot;
-  __shared__ double trace;
+// The round-robin order: at step k (mod 63) slot m of 32 holds the pair (p, q) =
+// (k, 63) for m = 0 and ((k + m) mod 63, (k - m) mod 63) otherwise; every
+// unordered pair meets in exactly one of 63 steps.
+__device__ __forceinline__ int rr_top(int k, int m) { return k + m < 63 ? k + m : k + m - 63; }
+__device__ __forceinline__ int rr_bot(int k, int m) { return m == 0 ? 63 : k - m >= 0 ? k - m : k - m + 63; }
+
+// Lane i gets lane i + 1's (i - 1's) double.
+template <int CTRL>
+__device__ __forceinline__ double wave_move(double x) {
+  const uint64_t u = __double_as_longlong(x);
+  const uint32_t lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(u), CTRL, 0xF, 0xF, false);
+  const uint32_t hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(u >> 32), CTRL, 0xF, 0xF, false);
+  return __longlong_as_double(static_cast<uint64_t>(hi) << 32 | lo);
+}
+__device__ __forceinline__ double wave_next(double x) { return wave_move<0x130>(x); }
+__device__ __forceinline__ double wave_prev(double x) { return wave_move<0x138>(x); }
+
+// One Newton step for y ~ 1 / sqrt(x).
+__device__ __forceinline__ double rsq_step(double x, double y) { return y * fma(-0.5 * x * y, y, 1.5); }
+
+// Eigenvectors of G_b (GU holds G on entry, U on return), one workgroup of 14
+// waves per 64-channel block.  What bounds it is the chain of steps: 500 or so,
+// each depending on the last.  So a step is one barrier long and three parts of
+// it run side by side:
+//  * wave 0 forms the next step's rotations, from this step's matrix and
+//    rotations (the three entries that each coming pair needs, ten old ones
+//    per pair) rather than waiting for the updated matrix;
+//  * waves 1-5 apply this step's rotations to the matrix, from one LDS buffer to
+//    the other, in 2 x 2 blocks of slot pairs (rows and columns at once); by
+//    symmetry only slot pairs at cyclic distance 0 .. 16 are computed, each
+//    written twice;
+//  * waves 6-13 rotate the accumulated vectors in registers: a lane is a slot
+//    and holds eight rows' pairs (four per half wave), and since the slots'
+//    contents move by one slot per step, the columns move by one lane.
+// 2560 x 2048 (32 blocks, 410 steps): 324 us, 0.8 us a step, the length of wave
+// 0's chain of fp64 operations.  (Before: parameters, column pass and row pass in turn through LDS with three
+// barriers, the Gram matrix on the vector units of the same 32 workgroups:
+// 1456 us with the Gram matrix, now 51 us in a kernel of its own.)
+__global__ __launch_bounds__(896) void block_eig_kernel(double* __restrict__ GU, double* __restrict__ lam) {
+  // The Jacobi iterate, double-buffered.  Rows unpadded: a lane's row and column both move by one
+  // per slot, up or down, so the lanes' addresses are 65 or 63 doubles apart: no bank conflicts
+  // (a row of 65 doubles would put them 64 apart, all on one bank).
+  __shared__ double A[2][kB][kB];
+  __shared__ double2 rot[2][32];     // (c, s) of the slots, double-buffered
+  __shared__ int done[2];
   __shared__ double dg[kB];
   __shared__ int rk[kB];
-  const int tid = threadIdx.x;
-  const int b = blockIdx.x;
-  if (tid < kB) {
-    const int32_t c = perm[b * kB + tid];  // clamped: an out-of-range entry cannot address outside the row
-    cols[tid] = c < 0 ? 0 : (c >= K ? static_cast<int>(K - 1) : c);
-  }
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m = lane & 31;
+  double* g = GU + static_cast<int64_t>(blockIdx.x) * kB * kB;
+  for (int i = tid; i < kB * kB; i += 896) A[0][i >> 6][i & 63] = g[i];
+  if (tid < 32) rot[0][tid] = make_double2(1.0, 0.0);
   __syncthreads();
+  double trace = 0.0;
+  for (int i = 0; i < kB; ++i) trace += A[0][i][i];
+  const double floor2 = 0x1p-104 * trace * trace;
 
-  // Gram matrix: thread t accumulates G[i][j0 .. j0 + 15], i = t / 4.
-  const int gi = tid >> 2, gj0 = (tid & 3) * 16;
-  double acc[16];
-#pragma unroll
-  for (int u = 0; u < 16; ++u) acc[u] = 0.0;
-  for (int64_t n0 = 0; n0 < N; n0 += 64) {
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const int idx = tid + 256 * u;          // 4096 entries of the chunk
-      const int rr = idx >> 6, cc = idx & 63;
-      const int64_t n = n0 + rr;
-      const int64_t nc = n < N ? n : N - 1;   // clamped row; its value is replaced by 0
-      const double v = h2d(W[nc * ldw + cols[cc]]);
-      X[rr][cc] = n < N ? v : 0.0;
+  // (wave 0) Rotations of step k + 1 (mod 63) from the matrix and rotations of
+  // step k.  A pair is rotated unless |a_pq| is negligible against the diagonal,
+  // |a_pq| <= 2^-53 sqrt(|a_pp a_qq|), or at the rounding level of the whole
+  // matrix, |a_pq| <= 2^-52 trace(G) (entries of a numerically null eigenspace
+  // would otherwise keep rotating among themselves).  The angle needs no last
+  // bit; c^2 + s^2 = 1 does, so c takes two Newton steps.  Returns whether any
+  // pair rotates.
+  auto next_rotations = [&](int x, int k) -> bool {
+    // Slots that hold the coming pair now: its top comes from the top of slot
+    // m + 1 (slot 31: its own bottom), its bottom from the bottom of slot m - 1
+    // (slot 1: the top of slot 0; slot 0 keeps 63).
+    const int sa = m < 31 ? m + 1 : 31, sb = m < 2 ? 0 : m - 1;
+    const double2 ra = rot[x][sa], rb = rot[x][sb];
+    const int ap = rr_top(k, sa), aq = rr_bot(k, sa), bp = rr_top(k, sb), bq = rr_bot(k, sb);
+    const double (*M)[kB] = A[x];
+    const double app = M[ap][ap], apq = M[ap][aq], aqq = M[aq][aq];
+    const double bpp = M[bp][bp], bpq = M[bp][bq], bqq = M[bq][bq];
+    const double x00 = M[ap][bp], x01 = M[ap][bq], x10 = M[aq][bp], x11 = M[aq][bq];
+    const double a0 = m < 31 ? ra.x : ra.y, a1 = m < 31 ? -ra.y : ra.x;    // top (c, -s) / bottom (s, c)
+    const double b0 = m == 1 ? rb.x : rb.y, b1 = m == 1 ? -rb.y : rb.x;
+    const double dp = a0 * a0 * app + 2.0 * a0 * a1 * apq + a1 * a1 * aqq;
+    const double dq = b0 * b0 * bpp + 2.0 * b0 * b1 * bpq + b1 * b1 * bqq;
+    const double o = a0 * (b0 * x00 + b1 * x01) + a1 * (b0 * x10 + b1 * x11);
+    double c = 1.0, s = 0.0;
+    // t = tan of the angle: the smaller root, sign(d) 2 o / (|d| + sqrt(d^2 + 4 o^2)).
+    if (o * o > fmax(0x1p-106 * fabs(dp * dq), floor2)) {
+      const double d = dq - dp, o2 = 2.0 * o, r = fma(d, d, o2 * o2);
+      const double den = fma(r, rsq_step(r, __builtin_amdgcn_rsq(r)), fabs(d));
+      double rc = __builtin_amdgcn_rcp(den);
+      rc = rc * fma(-den, rc, 2.0);
+      const double t = (d >= 0.0 ? o2 : -o2) * rc;
+      const double u = fma(t, t, 1.0);
+      c = rsq_step(u, rsq_step(u, __builtin_amdgcn_rsq(u)));
+      s = t * c;
+      if (s == 0.0) c = 1.0;
     }
-    __syncthreads();
-    for (int rr = 0; rr < 64; ++rr) {
-      const double xi = X[rr][gi];
-#pragma unroll
-      for (int u = 0; u < 16; ++u) acc[u] = fma(xi, X[rr][gj0 + u], acc[u]);
-    }
-    __syncthreads();
-  }
-#pragma unroll
-  for (int u = 0; u < 16; ++u) {
-    A[gi][gj0 + u] = acc[u];
-    V[gi][gj0 + u] = gi == gj0 + u ? 1.0 : 0.0;
-  }
-  __syncthreads();
-  if (tid == 0) {
-    double t = 0.0;
-    for (int i = 0; i < kB; ++i) t += A[i][i];
-    trace = t;
-  }
-  __syncthreads();
-  const double abs_floor = 0x1p-52 * trace;
+    if (lane < 32) rot[x ^ 1][m] = make_double2(c, s);
+    return __ballot(s != 0.0) != 0;
+  };
 
-  // Cyclic Jacobi.  A pair is rotated unless |a_pq| is negligible against
-  // the diagonal, |a_pq| <= 2^-53 sqrt(|a_pp a_qq|), or at the rounding level
-  // of the whole matrix, |a_pq| <= 2^-52 trace(G) (entries of a numerically
-  // null eigenspace would otherwise keep rotating among themselves).
-  for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
-    if (tid == 0) nrot = 0;
-    __syncthreads();
-    for (int k = 0; k < 63; ++k) {
-      if (tid < 32) {
-        int p, q;
-        rr_pair(k, tid, &p, &q);
-        const double app = A[p][p], aqq = A[q][q], apq = A[p][q];
-        double c = 1.0, s = 0.0;
-        if (apq != 0.0 && fabs(apq) > fmax(0x1p-53 * sqrt(fabs(app * aqq)), abs_floor)) {
-          const double theta = (aqq - app) / (2.0 * apq);
-          const double t = (theta >= 0.0 ? 1.0 : -1.0) / (fabs(theta) + sqrt(fma(theta, theta, 1.0)));
-          c = 1.0 / sqrt(fma(t, t, 1.0));
-          s = t * c;
-          if (s != 0.0) atomicAdd(&nrot, 1);
-          else c = 1.0;
-        }
-        pp[tid] = p;
-        pq[tid] = q;
-        pc[tid] = c;
-        ps[tid] = s;
+  // Rows 8 (wv - 6) + 4 (lane / 32) + j of V in slot order: top and bottom of slot m.
+  const int vr = 8 * (wv - 6) + 4 * (lane >> 5);
+  double vt[4], vb[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    vt[j] = vr + j == rr_top(0, m) ? 1.0 : 0.0;
+    vb[j] = vr + j == rr_bot(0, m) ? 1.0 : 0.0;
+  }
+
+  // Step 0's rotations: the identity applied to G as if at step 62.  (rot[0] is
+  // the identity; the result lands in rot[1], so the matrix moves there too.)
+  int idle = 0;  // (wave 0) steps in a row without a rotation
+  if (wv == 0) {
+    idle = next_rotations(0, 62) ? 0 : 1;
+    if (lane == 0) done[1] = 0;
+  }
+  for (int i = tid; i < kB * kB; i += 896) A[1][i >> 6][i & 63] = A[0][i >> 6][i & 63];
+  __syncthreads();
+  int k = 0, x = 1;
+  for (int step = 0; step < kMaxSteps && !done[x]; ++step) {
+    if (wv == 0) {
+      idle = next_rotations(x, k) ? 0 : idle + 1;
+      if (lane == 0) done[x ^ 1] = idle >= 63;
+    } else if (wv < 6) {
+      // Distances dist = 2 i + lane / 32, i = wv - 1 and wv + 4; both loaded before either is stored.
+      const double2 r1 = rot[x][m];
+      const int p1 = rr_top(k, m), q1 = rr_bot(k, m);
+      double2 r2[2];
+      int p2[2], q2[2];
+      double e00[2], e01[2], e10[2], e11[2];
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int m2 = (m + 2 * (wv - 1 + 5 * i) + (lane >> 5)) & 31;
+        r2[i] = rot[x][m2];
+        p2[i] = rr_top(k, m2);
+        q2[i] = rr_bot(k, m2);
+        e00[i] = A[x][p1][p2[i]];
+        e01[i] = A[x][p1][q2[i]];
+        e10[i] = A[x][q1][p2[i]];
+        e11[i] = A[x][q1][q2[i]];
       }
-      __syncthreads();
-      // Columns p, q of A and V (rows r, 64 x 32 items over 256 threads).
-      for (int it = tid; it < 64 * 32; it += 256) {
-        const int m = it & 31, r = it >> 5;
-        const int p = pp[m], q = pq[m];
-        const double c = pc[m], s = ps[m];
-        if (s != 0.0) {
-          const double arp = A[r][p], arq = A[r][q];
-          A[r][p] = c * arp - s * arq;
-          A[r][q] = s * arp + c * arq;
-          const double vrp = V[r][p], vrq = V[r][q];
-          V[r][p] = c * vrp - s * vrq;
-          V[r][q] = s * vrp + c * vrq;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        const int dist = 2 * (wv - 1 + 5 * i) + (lane >> 5);
+        const double f00 = r2[i].x * e00[i] - r2[i].y * e01[i], f01 = r2[i].y * e00[i] + r2[i].x * e01[i];
+        const double f10 = r2[i].x * e10[i] - r2[i].y * e11[i], f11 = r2[i].y * e10[i] + r2[i].x * e11[i];
+        const double h00 = r1.x * f00 - r1.y * f10, h11 = r1.y * f01 + r1.x * f11;
+        double h01 = r1.x * f01 - r1.y * f11, h10 = r1.y * f00 + r1.x * f10;
+        // In a slot's own block the rotated pair becomes exactly 0, and both off-diagonal entries one value.
+        if (dist == 0) {
+          if (r1.y != 0.0) h01 = 0.0;
+          h10 = h01;
+        }
+        if (dist < 16 || (dist == 16 && m < 16)) {
+          A[x ^ 1][p1][p2[i]] = h00;
+          A[x ^ 1][p1][q2[i]] = h01;
+          A[x ^ 1][q1][p2[i]] = h10;
+          A[x ^ 1][q1][q2[i]] = h11;
+          if (dist != 0) {
+            A[x ^ 1][p2[i]][p1] = h00;
+            A[x ^ 1][q2[i]][p1] = h01;
+            A[x ^ 1][p2[i]][q1] = h10;
+            A[x ^ 1][q2[i]][q1] = h11;
+          }
         }
       }
-      __syncthreads();
-      // Rows p, q of A.
-      for (int it = tid; it < 64 * 32; it += 256) {
-        const int m = it & 31, r = it >> 5;
-        const int p = pp[m], q = pq[m];
-        const double c = pc[m], s = ps[m];
-        if (s != 0.0) {
-          const double apr = A[p][r], aqr = A[q][r];
-          A[p][r] = c * apr - s * aqr;
-          A[q][r] = s * apr + c * aqr;
-        }
+    } else {
+      const double2 r = rot[x][m];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const double t = r.x * vt[j] - r.y * vb[j], bo = r.y * vt[j] + r.x * vb[j];
+        const double down = m == 0 ? t : bo;  // moves to the next slot's bottom
+        const double up = wave_next(t), pr = wave_prev(down);
+        vt[j] = m == 31 ? bo : up;
+        vb[j] = m == 0 ? bo : pr;
       }
-      __syncthreads();
     }
-    if (nrot == 0) break;  // read by every thread after the last barrier of the sweep
-    __syncthreads();       // nobody resets nrot before everyone has read it
+    __syncthreads();
+    x ^= 1;
+    k = k == 62 ? 0 : k + 1;
   }
 
   // Order and signs.
-  if (tid < kB) dg[tid] = A[tid][tid];
+  if (tid < kB) dg[tid] = A[x][tid][tid];
+  if (wv >= 6) {
+    const int p = rr_top(k, m), q = rr_bot(k, m);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      A[x ^ 1][vr + j][p] = vt[j];
+      A[x ^ 1][vr + j][q] = vb[j];
+    }
+  }
   __syncthreads();
+  const double (*V)[kB] = A[x ^ 1];
   if (tid < kB) {
     const double li = dg[tid];
     int r = 0;
     for (int j = 0; j < kB; ++j) r += (dg[j] > li || (dg[j] == li && j < tid)) ? 1 : 0;
     rk[tid] = r;
-    lam[static_cast<int64_t>(b) * kB + r] = li;
+    lam[static_cast<int64_t>(blockIdx.x) * kB + r] = li;
     int arg = 0;
     double best = -1.0;
     for (int rr = 0; rr < kB; ++rr) {
@@ -284,26 +406,28 @@ __global__ __launch_bounds__(256) void block_eig_kernel(const uint16_t* __restri
         arg = rr;
       }
     }
-    dg[tid] = V[arg][tid] < 0.0 ? -1.0 : 1.0;  // reuse: the sign of column tid
+    A[x][0][tid] = V[arg][tid] < 0.0 ? -1.0 : 1.0;  // (the iterate is spent) the sign of column tid
   }
   __syncthreads();
-  for (int it = tid; it < kB * kB; it += 256) {
+  for (int it = tid; it < kB * kB; it += 896) {
     const int r = it >> 6, i = it & 63;
-    U[(static_cast<int64_t>(b) * kB + r) * kB + rk[i]] = dg[i] * V[r][i];
+    g[r * kB + rk[i]] = A[x][0][i] * V[r][i];
   }
 }
 
-// Rt[b][j][r] = fp16(R_b[r][j]), R_b[r][j] = sum_i U_b[r][i] H[i][j] / 8.
-__global__ __launch_bounds__(256) void block_rot_kernel(const double* __restrict__ U, int nb,
-                                                        uint16_t* __restrict__ Rt) {
-  const int64_t idx = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  if (idx >= static_cast<int64_t>(nb) * kB * kB) return;
-  const int b = static_cast<int>(idx / (kB * kB));
-  const int j = static_cast<int>((idx / kB) % kB), r = static_cast<int>(idx % kB);
-  const double* ur = U + (static_cast<int64_t>(b) * kB + r) * kB;
+// Rt[b][j][r] = fp16(R_b[r][j]), R_b[r][j] = sum_i U_b[r][i] H[i][j] / 8: four
+// workgroups per block, a wave per column j, a lane per row r.
+__global__ __launch_bounds__(1024) void block_rot_kernel(const double* __restrict__ U, uint16_t* __restrict__ Rt) {
+  __shared__ double u[kB][kLd];
+  const int b = blockIdx.x >> 2, lane = threadIdx.x & 63;
+  const int j = (blockIdx.x & 3) * 16 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double* ub = U + static_cast<int64_t>(b) * kB * kB;
+  for (int i = threadIdx.x; i < kB * kB; i += 1024) u[i >> 6][i & 63] = ub[i];
+  __syncthreads();
   double s = 0.0;
-  for (int i = 0; i < kB; ++i) s += (__popc(i & j) & 1) ? -ur[i] : ur[i];
-  Rt[idx] = f64_to_f16_rne(s * 0.125);
+#pragma unroll 16
+  for (int i = 0; i < kB; ++i) s += (__popc(i & j) & 1) ? -u[lane][i] : u[lane][i];
+  Rt[(static_cast<int64_t>(b) * kB + j) * kB + lane] = f64_to_f16_rne(s * 0.125);
 }
 
 int check_weight(const void* W, int64_t N, int64_t K, int64_t ldw) {
@@ -322,7 +446,7 @@ extern "C" int oq_channel_energy(const void* W, int64_t N, int64_t K, int64_t ld
   if (!oq::aligned(W, 2) || !oq::aligned(energy, 8)) return OQ_ERR_ALIGN;
   int st = oq::device_check();
   if (st != OQ_OK) return st;
-  hipLaunchKernelGGL(oq::energy_kernel, dim3(static_cast<unsigned>((K + 63) / 64)), dim3(1024), 0,
+  hipLaunchKernelGGL(oq::energy_kernel, dim3(static_cast<unsigned>((K + 15) / 16)), dim3(1024), 0,
                      static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(W), N, K, ldw, energy);
   return oq::launch_status();
 }
@@ -333,7 +457,7 @@ extern "C" int oq_zigzag_permutation(const double* energy, int64_t K, int32_t bl
   if (!oq::aligned(energy, 8) || !oq::aligned(perm, 4)) return OQ_ERR_ALIGN;
   int st = oq::device_check();
   if (st != OQ_OK) return st;
-  hipLaunchKernelGGL(oq::zigzag_kernel, dim3(static_cast<unsigned>((K + 255) / 256)), dim3(256), 0,
+  hipLaunchKernelGGL(oq::zigzag_kernel, dim3(static_cast<unsigned>((K + 63) / 64)), dim3(1024), 0,
                      static_cast<hipStream_t>(stream), energy, static_cast<int>(K), static_cast<int>(K / block),
                      perm);
   return oq::launch_status();
@@ -347,8 +471,11 @@ extern "C" int oq_block_svd(const void* W, int64_t N, int64_t K, int64_t ldw, co
   if (!perm || !U || !sigma2) return OQ_ERR_NULL;
   if (!oq::aligned(perm, 4) || !oq::aligned(U, 8) || !oq::aligned(sigma2, 8)) return OQ_ERR_ALIGN;
   if ((st = oq::device_check()) != OQ_OK) return st;
-  hipLaunchKernelGGL(oq::block_eig_kernel, dim3(static_cast<unsigned>(K / oq::kB)), dim3(256), 0,
-                     static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(W), N, K, ldw, perm, U, sigma2);
+  // (U holds the Gram matrices in between.)
+  hipLaunchKernelGGL(oq::gram_kernel, dim3(static_cast<unsigned>(6 * (K / oq::kB))), dim3(512), 0,
+                     static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(W), N, K, ldw, perm, U);
+  hipLaunchKernelGGL(oq::block_eig_kernel, dim3(static_cast<unsigned>(K / oq::kB)), dim3(896), 0,
+                     static_cast<hipStream_t>(stream), U, sigma2);
   return oq::launch_status();
 }
 
@@ -358,9 +485,8 @@ extern "C" int oq_block_rotations(const double* U, int64_t K, int32_t block, uin
   if (!oq::aligned(U, 8) || !oq::aligned(Rt, 2)) return OQ_ERR_ALIGN;
   int st = oq::device_check();
   if (st != OQ_OK) return st;
-  const int64_t total = K * oq::kB;
-  hipLaunchKernelGGL(oq::block_rot_kernel, dim3(static_cast<unsigned>((total + 255) / 256)), dim3(256), 0,
-                     static_cast<hipStream_t>(stream), U, static_cast<int>(K / oq::kB), Rt);
+  hipLaunchKernelGGL(oq::block_rot_kernel, dim3(static_cast<unsigned>(4 * (K / oq::kB))), dim3(1024), 0,
+                     static_cast<hipStream_t>(stream), U, Rt);
   return oq::launch_status();
 }
 
