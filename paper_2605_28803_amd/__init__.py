@@ -33,9 +33,18 @@ def _check(status: int, where: str):
         raise OQError(status, where)
 
 
+# The current stream's handle without building a torch.cuda.Stream, and plain integers for
+# pointers (the prototypes convert them): a call's host time bounds the smallest linears
+# (64 x 1024 x 1024, two calls: 16.1 us with Stream and c_void_p objects, 11.0 us without).
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return C.c_void_p(s.cuda_stream)
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 def _ld(t):
@@ -47,7 +56,7 @@ def _ld(t):
 
 
 def _ptr(t):
-    return None if t is None else C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _s_table(s_table):
