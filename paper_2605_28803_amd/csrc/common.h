@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <utility>
+
 #include "oq.h"
 
 namespace oq {
@@ -22,6 +24,16 @@ inline int ilog2(int64_t n) {
 inline int launch_status() {
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? OQ_OK : OQ_ERR_HIP;
+}
+
+// f(std::integral_constant<int, i>) for i = 0 .. N-1, fully unrolled.
+template <typename F, int... I>
+__device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F&& f) {
+  static_for_seq(f, std::make_integer_sequence<int, N>{});
 }
 
 // ---- 16-row tiled code layout -----------------------------------------------

@@ -444,18 +444,23 @@ __global__ __launch_bounds__(512) void rq_composite1_kernel(const uint16_t* __re
 // that each block matrix R_b is read once per R rows instead of once per few
 // rows.  The nq workgroups of a
 // tile exchange their rows' partial maxima through per-launch slots in global
-// memory (initialised to -1 by comp_prep_kernel; a published maximum is >= 0)
+// memory (initialised to -1 by comp_slots_kernel; a published maximum is >= 0)
 // and each quantizes its own chunk, so every y value is computed once and
 // stays in registers.
 //
-// Staging: each thread owns K / 8 / 512 pieces of 8 input channels; with the
-// online permutation it looks up the permuted position j = P^-1(k) of each of
-// its channels once (pinv, written by comp_prep_kernel) and, for every row,
-// loads the piece with one 16-byte read and writes the channels whose j falls
-// in this chunk to LDS at j - qC.  The whole row is read by each of the nq
-// workgroups (from L2: the tile's workgroups are placed on one XCD, adjacent
-// in dispatch order).  Without a permutation the chunk's columns are copied
-// directly.
+// Staging with the online permutation: a row at a time goes through registers
+// (16-byte loads, four rows ahead) into a raw LDS row, from which each thread
+// gathers the C / 512 channels of its consecutive positions (2-byte LDS reads)
+// and stores them with one write into the chunk's row.  The whole row is read
+// by each of the nq workgroups (from L2: the tile's workgroups are placed on
+// one XCD, adjacent in dispatch order).  What the other forms are bound by:
+// storing from registers the channels that fall into the chunk under a mask
+// keeps 1 / nq of the store lanes at work (4080 x 16384: 166 us); loading them
+// from global memory 2 bytes each in source order runs at one lane per clock
+// (120 us); this, with the block matrices and the packing below, takes 84 us.  At C = 4096 and K = 16384 the two buffers are
+// all of the LDS, so the chunk's rows are not padded: 16-byte piece p of row r
+// is stored at p ^ r, which spreads the operand reads of 16 rows over the banks.
+// Without a permutation the chunk's columns are copied directly into padded rows.
 //
 // Exchange: the tile's workgroups are dispatched together (ids x + 8 (nq t' +
 // q) for XCD x), so a workgroup only waits for partners dispatched at the same
@@ -465,30 +470,40 @@ __global__ __launch_bounds__(512) void rq_composite1_kernel(const uint16_t* __re
 // ---------------------------------------------------------------------------
 constexpr int kPollLimit = 1 << 20;
 
-__global__ __launch_bounds__(256) void comp_prep_kernel(const int32_t* __restrict__ perm, int K,
-                                                        uint16_t* __restrict__ pinv, float* __restrict__ slots,
-                                                        int64_t nslots) {
-  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
-  // A perm entry out of range is clamped, so every write stays inside pinv
-  // (a non-permutation gives wrong codes, never an access out of bounds).
-  if (perm && i < K) pinv[min(max(perm[i], 0), K - 1)] = static_cast<uint16_t>(i);
-  if (i < nslots) slots[i] = -1.0f;
+// Workgroup barrier for LDS alone: loads from global memory stay in flight
+// (__syncthreads waits for them).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
+__global__ __launch_bounds__(1024) void comp_slots_kernel(float* __restrict__ slots, int64_t nslots) {
+  for (int64_t i = static_cast<int64_t>(blockIdx.x) * 1024 + threadIdx.x; i < nslots;
+       i += static_cast<int64_t>(gridDim.x) * 1024)
+    slots[i] = -1.0f;
 }
 
 template <int RG, int C, bool GATHER, int WAVES, int PF>
 __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
-    const uint16_t* __restrict__ X, int64_t M, int K, int64_t ldx, const uint16_t* __restrict__ pinv,
+    const uint16_t* __restrict__ X, int64_t M, int K, int64_t ldx, const int32_t* __restrict__ perm,
     const uint16_t* __restrict__ Rt, float s_t, uint8_t* __restrict__ Xq, float* __restrict__ xs,
     float* __restrict__ slots, int nq, int ntiles) {
   constexpr int NT = 64 * WAVES;
-  constexpr int R = 16 * RG, XS = C + 8;
+  constexpr int R = 16 * RG, XS = C;
   constexpr int NBC = C / kCB, NBW = NBC / WAVES;  // blocks per chunk, per wave
   static_assert(NBW >= 1 && NBC % WAVES == 0, "chunk blocks per wave");
   static_assert(PF >= 2, "block matrix ring depth");
-  __shared__ __attribute__((aligned(16))) uint16_t sx[R * XS];
-  __shared__ float red[WAVES][R];
-  __shared__ float gscale[R];
-  __shared__ int timed_out;
+  // The chunk's rows (later the codes); then a region for, in turn, the raw row
+  // (with the permutation), 2 KB of block matrix per wave, the maxima and scales.
+  constexpr int AUXB = GATHER ? 2 * 16384 : WAVES * 2048;
+  __shared__ __attribute__((aligned(16))) uint8_t smem[R * XS * 2 + AUXB];
+  static_assert((WAVES * R + R + 1) * 4 <= AUXB && WAVES * 2048 <= AUXB, "auxiliary region");
+  uint16_t* sx = reinterpret_cast<uint16_t*>(smem);
+  uint16_t* raw = sx + R * XS;
+  float (*red)[R] = reinterpret_cast<float (*)[R]>(raw);
+  float* gscale = reinterpret_cast<float*>(raw) + WAVES * R;
+  int& timed_out = *reinterpret_cast<int*>(gscale + R);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
@@ -497,86 +512,68 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
   if (tile >= ntiles) return;  // every workgroup of such a tile id returns
   const int64_t row0 = static_cast<int64_t>(tile) * R;
   const int cbase = q * C;
-  if (tid == 0) timed_out = 0;
 
   // ---- y = x_chunk . BlockDiag(R_b) for this wave's NBW blocks, kept in
   // registers.  The block matrices run through a ring of PF register stages;
   // the first PF - 1 are requested before the rows are staged.
   const int r16 = lane & 15, qq = lane >> 4;
   const int wb0 = wave * NBW;  // first block of this wave within the chunk
+  // (Block matrices are loaded as they lie in memory, 1 KB of consecutive bytes
+  // per instruction, and turned into operands through LDS: loaded directly, the
+  // lanes of an operand are 128 bytes apart and a load takes 64 cycles instead of 16.)
   auto load_b = [&](int i, c8h (&f)[4][2]) {
-    const int64_t gb = static_cast<int64_t>(q) * NBC + wb0 + (i < NBW ? i : 0);
+    const uint16_t* rb = Rt + (static_cast<int64_t>(q) * NBC + wb0 + (i < NBW ? i : 0)) * kCB * kCB + 8 * lane;
 #pragma unroll
     for (int cb = 0; cb < 4; ++cb)
 #pragma unroll
-      for (int kk = 0; kk < 2; ++kk)
-        f[cb][kk] = *reinterpret_cast<const c8h*>(Rt + (gb * kCB + cb * 16 + r16) * kCB + kk * 32 + 8 * qq);
+      for (int h = 0; h < 2; ++h) f[cb][h] = *reinterpret_cast<const c8h*>(rb + cb * 1024 + h * 512);
   };
   c8h bring[PF][4][2];
 #pragma unroll
   for (int i = 0; i < PF - 1; ++i)
     if (i < NBW) load_b(i, bring[i]);
-  // ---- Stage the chunk of R rows in LDS (rows past M as zeros).
+  // ---- Stage the chunk of R rows in LDS (rows past M read row M - 1; their
+  // results are not stored).
   if constexpr (GATHER) {
-    const int npc = K / 8;                       // pieces per row
-    constexpr int PMAX = 16384 / 8 / NT;         // pieces per thread at K = 16384
-    const int ppc = (npc + NT - 1) / NT;         // pieces per thread here
-    uint32_t dst[PMAX][4];                       // local positions of the 8 channels, 2 per word, 0xFFFF = none
+    constexpr int EPT = C / NT;                  // positions per thread
+    static_assert(EPT >= 1 && C % NT == 0, "positions per thread");
+    typedef uint16_t vec __attribute__((ext_vector_type(EPT)));
+    int idx[EPT];                                // their channels (clamped: never outside the row)
 #pragma unroll
-    for (int pi = 0; pi < PMAX; ++pi) {
-      const int p = tid + NT * pi;
-      uint4 pv = make_uint4(0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu, 0xFFFFFFFFu);
-      if (pi < ppc && p < npc) pv = *reinterpret_cast<const uint4*>(pinv + 8 * p);
-      const uint32_t w[4] = {pv.x, pv.y, pv.z, pv.w};
+    for (int e = 0; e < EPT; ++e) idx[e] = min(max(perm[cbase + tid * EPT + e], 0), K - 1);
+    constexpr int PMAX = 16384 / 8 / NT;         // 16-byte pieces of a row per thread at K = 16384
+    constexpr int AHEAD = 4;
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    u4 v[AHEAD][PMAX];
+#define OQ_LOAD_ROW(RR, S)                                                                     \
+  {                                                                                            \
+    const int64_t gr_ = row0 + (RR) < M ? row0 + (RR) : M - 1;                                 \
+    const uint16_t* xr_ = X + gr_ * ldx;                                                       \
+    _Pragma("unroll") for (int i_ = 0; i_ < PMAX; ++i_) {                                      \
+      const int p_ = tid + NT * i_;                                                            \
+      v[S][i_] = *reinterpret_cast<const u4*>(xr_ + (8 * p_ < K ? 8 * p_ : 0));              \
+    }                                                                                          \
+  }
+    static_for<AHEAD>([&](auto S_) { OQ_LOAD_ROW(decltype(S_)::value, decltype(S_)::value) });
+    static_for<R>([&](auto R_) {  // (constant ring slots: the loads stay in registers)
+      constexpr int r = decltype(R_)::value, sl = r % AHEAD;
 #pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        uint32_t lo = (w[c] & 0xFFFFu) - cbase, hi = (w[c] >> 16) - cbase;
-        lo = (pi < ppc && p < npc && lo < static_cast<uint32_t>(C)) ? lo : 0xFFFFu;
-        hi = (pi < ppc && p < npc && hi < static_cast<uint32_t>(C)) ? hi : 0xFFFFu;
-        dst[pi][c] = lo | (hi << 16);
+      for (int i = 0; i < PMAX; ++i)
+        *reinterpret_cast<u4*>(raw + 8 * (tid + NT * i)) = v[sl][i];  // (past K: never gathered)
+      if constexpr (r + AHEAD < R) OQ_LOAD_ROW(r + AHEAD, sl)
+      lds_barrier();
+      vec g;
+      if constexpr (EPT == 1) {
+        g = raw[idx[0]];
+      } else {
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) g[e] = raw[idx[e]];
       }
-    }
-    // Rows in batches of RB, double-buffered: the loads of batch b + 1 are
-    // issued before batch b is written to LDS.
-    constexpr int RB = 4;
-    static_assert(R % RB == 0, "row batches");
-    uint4 v[2][RB][PMAX];
-    auto load_rows = [&](int r0, uint4 (&buf)[RB][PMAX]) {
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        const int64_t gr = row0 + r0 + rb;
-        const bool rok = gr < M;
-#pragma unroll
-        for (int pi = 0; pi < PMAX; ++pi) {
-          const int p = tid + NT * pi;
-          const bool ok = rok && pi < ppc && p < npc;
-          buf[rb][pi] = *reinterpret_cast<const uint4*>(X + (ok ? gr : 0) * ldx + (ok ? 8 * p : 0));
-          if (!ok) buf[rb][pi] = make_uint4(0, 0, 0, 0);
-        }
-      }
-    };
-    load_rows(0, v[0]);
-#pragma unroll
-    for (int bt = 0; bt < R / RB; ++bt) {
-      if (bt + 1 < R / RB) load_rows((bt + 1) * RB, v[(bt + 1) & 1]);
-#pragma unroll
-      for (int rb = 0; rb < RB; ++rb) {
-        uint16_t* srow = sx + (bt * RB + rb) * XS;
-#pragma unroll
-        for (int pi = 0; pi < PMAX; ++pi) {
-          const uint4 x4 = v[bt & 1][rb][pi];
-          const uint32_t w[4] = {x4.x, x4.y, x4.z, x4.w};
-#pragma unroll
-          for (int c = 0; c < 4; ++c) {
-            const uint32_t lo = dst[pi][c] & 0xFFFFu, hi = dst[pi][c] >> 16;
-            if (lo != 0xFFFFu) srow[lo] = static_cast<uint16_t>(w[c]);
-            if (hi != 0xFFFFu) srow[hi] = static_cast<uint16_t>(w[c] >> 16);
-          }
-        }
-      }
-    }
-    // A permutation gives every position of the chunk exactly one channel, so
-    // every LDS element of the R rows is written (rows past M with zeros).
+      const int at = tid * EPT;                  // piece at / 8 moves to (at / 8) ^ (r mod 16)
+      *reinterpret_cast<vec*>(sx + r * XS + (at ^ ((r & 15) * 8))) = g;
+      lds_barrier();
+    });
+#undef OQ_LOAD_ROW
   } else {
     // The chunk's columns of each row go straight from global memory into
     // LDS (global_load_lds_dwordx4: lane l's 16 bytes land at the given LDS
@@ -587,7 +584,7 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
     for (int j = wave; j < R * PARTS; j += WAVES) {
       const int r = j / PARTS, h = j % PARTS;
       const int64_t gr = row0 + r < M ? row0 + r : M - 1;
-      const uint16_t* src = X + gr * ldx + cbase + 512 * h + 8 * lane;
+      const uint16_t* src = X + gr * ldx + cbase + 512 * h + 8 * (lane ^ (r & 15));
       __builtin_amdgcn_global_load_lds((gmem_void*)src, (lds_void*)(sx + r * XS + 512 * h), 16, 0, 0);
     }
     __builtin_amdgcn_s_waitcnt(0);
@@ -600,26 +597,50 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
   for (int rg = 0; rg < RG; ++rg)
 #pragma unroll
     for (int e = 0; e < 4; ++e) amax[rg][e] = 0.0f;
+  // This wave's 2 KB of the auxiliary region hold 16 columns at a time: column c of
+  // 128 bytes, its 16-byte piece p at slot p ^ (c / 2).  (A wave's LDS operations
+  // execute in order, so the next columns may be stored behind the reads.)
+  uint16_t* wbuf = raw + wave * 1024;
+  const int wslot = (lane >> 3) * 64, wp = lane & 7;
+  const int rslot = r16 * 64, rsw = (r16 >> 1) & 7;
 #pragma unroll
   for (int i = 0; i < NBW; ++i) {
     if (i + PF - 1 < NBW) load_b(i + PF - 1, bring[(i + PF - 1) % PF]);
     __builtin_amdgcn_sched_barrier(0);
     const c8h (&bf)[4][2] = bring[i % PF];
+    c8h a[RG][2];
 #pragma unroll
     for (int rg = 0; rg < RG; ++rg) {
-      const uint16_t* ap = &sx[(rg * 16 + r16) * XS + (wb0 + i) * kCB + 8 * qq];
-      const c8h a0 = *reinterpret_cast<const c8h*>(ap);
-      const c8h a1 = *reinterpret_cast<const c8h*>(ap + 32);
+      const uint16_t* ap = &sx[(rg * 16 + r16) * XS];
+      const int at = (wb0 + i) * kCB + 8 * qq;
+      a[rg][0] = *reinterpret_cast<const c8h*>(ap + (at ^ (r16 * 8)));
+      a[rg][1] = *reinterpret_cast<const c8h*>(ap + ((at + 32) ^ (r16 * 8)));
+    }
+    c8h b[4][2];
 #pragma unroll
-      for (int cb = 0; cb < 4; ++cb) {
-        c4f acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a0, bf[cb][0], c4f{0, 0, 0, 0}, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a1, bf[cb][1], acc, 0, 0, 0);
+    for (int cb = 0; cb < 4; ++cb) {
+#pragma unroll
+      for (int h = 0; h < 2; ++h)  // columns 8 h + lane / 8
+        *reinterpret_cast<c8h*>(wbuf + h * 512 + wslot + ((wp ^ (4 * h + (lane >> 4))) * 8)) = bf[cb][h];
+      asm volatile("" ::: "memory");
+#pragma unroll
+      for (int kk = 0; kk < 2; ++kk)
+        b[cb][kk] = *reinterpret_cast<const c8h*>(wbuf + rslot + (((4 * kk + qq) ^ rsw) * 8));
+      asm volatile("" ::: "memory");
+    }
+#pragma unroll
+    for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+      for (int rg = 0; rg < RG; ++rg) {
+        c4f acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[rg][0], b[cb][0], c4f{0, 0, 0, 0}, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(a[rg][1], b[cb][1], acc, 0, 0, 0);
         y[i][cb][rg] = acc;
 #pragma unroll
         for (int e = 0; e < 4; ++e) amax[rg][e] = fmaxf(amax[rg][e], fabsf(acc[e]));
       }
-    }
   }
+  __syncthreads();  // the waves' block matrices are spent: the region holds the maxima and scales
+  if (tid == 0) timed_out = 0;
   // Chunk maxima per row: across the 16 lanes of a row group, then the waves.
 #pragma unroll
   for (int rg = 0; rg < RG; ++rg)
@@ -674,25 +695,35 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
   __syncthreads();
 
   // ---- Codes: 8 consecutive channels packed into a dword across lanes and
-  // staged in LDS (the chunk's rows, C / 2 bytes each), then stored as 16-byte pieces.
+  // staged in LDS (the chunk's rows, C / 2 bytes each), then stored as 16-byte
+  // pieces.  A lane's four rows travel together, one per byte: lane pairs form
+  // a row's two nibbles, then two byte exchanges (lane ^ 2, ^ 4) leave lanes 0,
+  // 4, 2, 6 of eight with the dword of rows 0, 1, 2, 3.
   uint32_t* scodes = reinterpret_cast<uint32_t*>(sx);  // [R][C / 8] dwords
+  const uint32_t sel2 = (lane & 2) ? 0x03070206u : 0x05010400u;
+  const uint32_t sel4 = (lane & 4) ? 0x03020706u : 0x05040100u;
+  const int crow = 4 * qq + (lane & 2) + ((lane >> 2) & 1);
 #pragma unroll
-  for (int i = 0; i < NBW; ++i)
+  for (int rg = 0; rg < RG; ++rg) {
+    float g[4];
 #pragma unroll
-    for (int rg = 0; rg < RG; ++rg)
+    for (int e = 0; e < 4; ++e) g[e] = gscale[rg * 16 + 4 * qq + e];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int row = rg * 16 + 4 * qq + e;
-        const float g = gscale[row];
+    for (int i = 0; i < NBW; ++i)
 #pragma unroll
-        for (int cb = 0; cb < 4; ++cb) {
-          uint32_t c = __float_as_uint(fmaf(y[i][cb][rg][e], g, rqd::kRoundMagic)) & 0xFu;
-          c |= __float_as_uint(rqd::lane_xor<1>(__uint_as_float(c))) << 4;
-          c |= __float_as_uint(rqd::lane_xor<2>(__uint_as_float(c))) << 8;
-          c |= __float_as_uint(rqd::lane_xor<4>(__uint_as_float(c))) << 16;
-          if ((r16 & 7) == 0) scodes[row * (C / 8) + ((wb0 + i) * kCB + cb * 16 + r16) / 8] = c;
-        }
+      for (int cb = 0; cb < 4; ++cb) {
+        uint32_t c[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) c[e] = __float_as_uint(fmaf(y[i][cb][rg][e], g[e], rqd::kRoundMagic));
+        const uint32_t v = (__builtin_amdgcn_perm(c[1], c[0], 0x0C0C0400u) |
+                            __builtin_amdgcn_perm(c[3], c[2], 0x04000C0Cu)) & 0x0F0F0F0Fu;
+        const uint32_t w = v | __float_as_uint(rqd::lane_xor<1>(__uint_as_float(v))) << 4;
+        const uint32_t h = __builtin_amdgcn_perm(__float_as_uint(rqd::lane_xor<2>(__uint_as_float(w))), w, sel2);
+        const uint32_t d = __builtin_amdgcn_perm(__float_as_uint(rqd::lane_xor_dpp<4>(__uint_as_float(h))), h, sel4);
+        if ((lane & 1) == 0)
+          scodes[(rg * 16 + crow) * (C / 8) + ((wb0 + i) * kCB + cb * 16 + (r16 & 8)) / 8] = d;
       }
+  }
   __syncthreads();
   constexpr int CPR = C / 32;  // 16-byte code pieces per row of the chunk
   for (int p = tid; p < R * CPR; p += NT) {
@@ -703,8 +734,7 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
   }
 }
 
-// Device workspace of the chunked kernel (the inverse permutation and the
-// exchange slots), one per GPU, grown on demand and kept for the process.
+// Device workspace of the chunked kernel (the exchange slots), one per GPU, grown on demand and kept for the process.
 struct CompWork {
   void* ptr = nullptr;
   size_t bytes = 0;
@@ -741,23 +771,21 @@ int launch_composite_x(const void* X, int64_t M, int64_t K, int64_t ldx, const i
   const int64_t ntiles = (M + R - 1) / R;
   const int nq = static_cast<int>(K / C);
   if (ntiles > (int64_t{1} << 26)) return OQ_ERR_SHAPE;
-  const size_t pinv_bytes = (static_cast<size_t>(K) * 2 + 255) / 256 * 256;
   const int64_t nslots = nq > 1 ? ntiles * nq * R : 0;
-  void* ws = nullptr;
-  int st = comp_workspace(pinv_bytes + static_cast<size_t>(nslots) * 4 + 256, &ws);
-  if (st != OQ_OK) return st;
-  uint16_t* pinv = static_cast<uint16_t*>(ws);
-  float* slots = reinterpret_cast<float*>(static_cast<uint8_t*>(ws) + pinv_bytes);
-  const int64_t nprep = std::max<int64_t>(GATHER ? K : 0, nslots);
-  if (nprep > 0) {
-    hipLaunchKernelGGL(comp_prep_kernel, dim3(static_cast<unsigned>((nprep + 255) / 256)), dim3(256), 0, stream,
-                       GATHER ? perm : nullptr, static_cast<int>(K), pinv, slots, nslots);
+  float* slots = nullptr;
+  if (nslots > 0) {
+    void* ws = nullptr;
+    int st = comp_workspace(static_cast<size_t>(nslots) * 4, &ws);
+    if (st != OQ_OK) return st;
+    slots = static_cast<float*>(ws);
+    const int64_t nwg = std::min<int64_t>((nslots + 1023) / 1024, 256);
+    hipLaunchKernelGGL(comp_slots_kernel, dim3(static_cast<unsigned>(nwg)), dim3(1024), 0, stream, slots, nslots);
     if ((st = launch_status()) != OQ_OK) return st;
   }
   const int64_t grid = (ntiles + 7) / 8 * 8 * nq;
   hipLaunchKernelGGL((rq_composite_x_kernel<RG, C, GATHER, WAVES, PF>), dim3(static_cast<unsigned>(grid)),
                      dim3(64 * WAVES), 0, stream, static_cast<const uint16_t*>(X), M, static_cast<int>(K), ldx,
-                     pinv, static_cast<const uint16_t*>(Rt), s, Xq, x_scale, slots, nq,
+                     perm, static_cast<const uint16_t*>(Rt), s, Xq, x_scale, slots, nq,
                      static_cast<int>(ntiles));
   return launch_status();
 }

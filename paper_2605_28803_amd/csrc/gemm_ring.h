@@ -48,8 +48,6 @@
 // the barrier that publishes it.  The compiler's own counts only become
 // stricter by loads it does not see.
 #pragma once
-#include <utility>
-
 #include "common.h"
 
 namespace oq {
@@ -62,16 +60,6 @@ __device__ __forceinline__ uint16_t f32_to_bf16_rne(float f) {
   uint32_t b = __float_as_uint(f);
   b += 0x7FFFu + ((b >> 16) & 1u);
   return static_cast<uint16_t>(b >> 16);
-}
-
-// f(std::integral_constant<int, i>) for i = 0 .. N-1, fully unrolled.
-template <typename F, int... I>
-__device__ __forceinline__ void static_for_seq(F&& f, std::integer_sequence<int, I...>) {
-  (f(std::integral_constant<int, I>{}), ...);
-}
-template <int N, typename F>
-__device__ __forceinline__ void static_for(F&& f) {
-  static_for_seq(f, std::make_integer_sequence<int, N>{});
 }
 
 // Map a linear workgroup id to an output tile (tm, tn): consecutive ids go to
