@@ -7,11 +7,12 @@
 // scalar form): z = s_t y, Delta = max|z| / 7, q = round_half_even(z / Delta),
 // x_scale = Delta / s_t.
 //
-// Three kernels.  Up to K = 4096, rq_composite1_kernel keeps whole rows in
-// LDS and every y value in registers (one pass).  Above, rq_composite_x_kernel
-// splits each row into chunks of channels whose workgroups exchange their
-// partial row maxima (one pass, each y computed once); K that no chunk width
-// divides takes the two-pass rq_composite_kernel described next.
+// Three kernels.  rq_composite_x_kernel takes rows of one chunk (K = 512, 1024,
+// 1536, 2048, 3072, 4096: every y in registers, one pass), and above K = 4096
+// rows split into chunks of channels whose workgroups exchange their partial
+// row maxima (one pass, each y computed once).  Other K up to 4096 take
+// rq_composite1_kernel (whole rows in LDS, one pass), other K above it the
+// two-pass rq_composite_kernel described next.
 //
 // Two-pass kernel: one workgroup of four waves owns RW rows.  The rows are
 // staged in LDS as fp16.  Pass 1: wave w takes the 64-channel blocks b = w, w + 4, ...; for
@@ -484,7 +485,7 @@ __global__ __launch_bounds__(1024) void comp_slots_kernel(float* __restrict__ sl
     slots[i] = -1.0f;
 }
 
-template <int RG, int C, bool GATHER, int WAVES, int PF>
+template <int RG, int C, bool GATHER, int WAVES, int PF, int KMAX>
 __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
     const uint16_t* __restrict__ X, int64_t M, int K, int64_t ldx, const int32_t* __restrict__ perm,
     const uint16_t* __restrict__ Rt, float s_t, uint8_t* __restrict__ Xq, float* __restrict__ xs,
@@ -494,9 +495,11 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
   constexpr int NBC = C / kCB, NBW = NBC / WAVES;  // blocks per chunk, per wave
   static_assert(NBW >= 1 && NBC % WAVES == 0, "chunk blocks per wave");
   static_assert(PF >= 2, "block matrix ring depth");
-  // The chunk's rows (later the codes); then a region for, in turn, the raw row
+  // The chunk's rows (later the codes); then a region for, in turn, the raw rows
   // (with the permutation), 2 KB of block matrix per wave, the maxima and scales.
-  constexpr int AUXB = GATHER ? 2 * 16384 : WAVES * 2048;
+  // RPS raw rows (KMAX >= K channels each) are staged at a time.
+  constexpr int RPS = KMAX >= 1024 ? 16384 / KMAX : 16;
+  constexpr int AUXB = GATHER && RPS * KMAX * 2 > WAVES * 2048 ? RPS * KMAX * 2 : WAVES * 2048;
   __shared__ __attribute__((aligned(16))) uint8_t smem[R * XS * 2 + AUXB];
   static_assert((WAVES * R + R + 1) * 4 <= AUXB && WAVES * 2048 <= AUXB, "auxiliary region");
   uint16_t* sx = reinterpret_cast<uint16_t*>(smem);
@@ -537,43 +540,53 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
   if constexpr (GATHER) {
     constexpr int EPT = C / NT;                  // positions per thread
     static_assert(EPT >= 1 && C % NT == 0, "positions per thread");
-    typedef uint16_t vec __attribute__((ext_vector_type(EPT)));
+    // Stored VW at a time, so that a store stays within a 16-byte piece.
+    constexpr int VW = EPT % 8 == 0 ? 8 : EPT % 4 == 0 ? 4 : EPT % 2 == 0 ? 2 : 1;
+    typedef uint16_t vec __attribute__((ext_vector_type(VW)));
     int idx[EPT];                                // their channels (clamped: never outside the row)
 #pragma unroll
     for (int e = 0; e < EPT; ++e) idx[e] = min(max(perm[cbase + tid * EPT + e], 0), K - 1);
-    constexpr int PMAX = 16384 / 8 / NT;         // 16-byte pieces of a row per thread at K = 16384
-    constexpr int AHEAD = 4;
+    static_assert(R % RPS == 0, "rows per step");
+    constexpr int STEPS = R / RPS, AHEAD = STEPS < 4 ? STEPS : 4;
+    constexpr int PPR = KMAX / 8;                // 16-byte pieces of a raw row
+    constexpr int PMAX = RPS * PPR / NT;         // pieces of a step per thread
     typedef uint32_t u4 __attribute__((ext_vector_type(4)));
     u4 v[AHEAD][PMAX];
-#define OQ_LOAD_ROW(RR, S)                                                                     \
+#define OQ_LOAD_STEP(ST, S)                                                                    \
   {                                                                                            \
-    const int64_t gr_ = row0 + (RR) < M ? row0 + (RR) : M - 1;                                 \
-    const uint16_t* xr_ = X + gr_ * ldx;                                                       \
     _Pragma("unroll") for (int i_ = 0; i_ < PMAX; ++i_) {                                      \
-      const int p_ = tid + NT * i_;                                                            \
-      v[S][i_] = *reinterpret_cast<const u4*>(xr_ + (8 * p_ < K ? 8 * p_ : 0));              \
+      const int p_ = tid + NT * i_, rl_ = (ST) * RPS + p_ / PPR, c_ = p_ % PPR;                \
+      const int64_t gr_ = row0 + rl_ < M ? row0 + rl_ : M - 1;                                 \
+      v[S][i_] = *reinterpret_cast<const u4*>(X + gr_ * ldx + (8 * c_ < K ? 8 * c_ : 0));      \
     }                                                                                          \
   }
-    static_for<AHEAD>([&](auto S_) { OQ_LOAD_ROW(decltype(S_)::value, decltype(S_)::value) });
-    static_for<R>([&](auto R_) {  // (constant ring slots: the loads stay in registers)
-      constexpr int r = decltype(R_)::value, sl = r % AHEAD;
+    static_for<AHEAD>([&](auto S_) { OQ_LOAD_STEP(decltype(S_)::value, decltype(S_)::value) });
+    static_for<STEPS>([&](auto R_) {  // (constant ring slots: the loads stay in registers)
+      constexpr int st = decltype(R_)::value, sl = st % AHEAD;
 #pragma unroll
       for (int i = 0; i < PMAX; ++i)
         *reinterpret_cast<u4*>(raw + 8 * (tid + NT * i)) = v[sl][i];  // (past K: never gathered)
-      if constexpr (r + AHEAD < R) OQ_LOAD_ROW(r + AHEAD, sl)
+      if constexpr (st + AHEAD < STEPS) OQ_LOAD_STEP(st + AHEAD, sl)
       lds_barrier();
-      vec g;
-      if constexpr (EPT == 1) {
-        g = raw[idx[0]];
-      } else {
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) g[e] = raw[idx[e]];
+      for (int rl = 0; rl < RPS; ++rl) {
+        const int r = st * RPS + rl;
+#pragma unroll
+        for (int e0 = 0; e0 < EPT; e0 += VW) {
+          vec g;
+          if constexpr (VW == 1) {
+            g = raw[rl * KMAX + idx[e0]];
+          } else {
+#pragma unroll
+            for (int e = 0; e < VW; ++e) g[e] = raw[rl * KMAX + idx[e0 + e]];
+          }
+          const int at = tid * EPT + e0;         // piece at / 8 moves to (at / 8) ^ (r mod 16)
+          *reinterpret_cast<vec*>(sx + r * XS + (at ^ ((r & 15) * 8))) = g;
+        }
       }
-      const int at = tid * EPT;                  // piece at / 8 moves to (at / 8) ^ (r mod 16)
-      *reinterpret_cast<vec*>(sx + r * XS + (at ^ ((r & 15) * 8))) = g;
       lds_barrier();
     });
-#undef OQ_LOAD_ROW
+#undef OQ_LOAD_STEP
   } else {
     // The chunk's columns of each row go straight from global memory into
     // LDS (global_load_lds_dwordx4: lane l's 16 bytes land at the given LDS
@@ -764,7 +777,7 @@ int comp_workspace(size_t bytes, void** out) {
   return OQ_OK;
 }
 
-template <int RG, int C, bool GATHER, int WAVES = 8, int PF = 2>
+template <int RG, int C, bool GATHER, int KMAX = C, int WAVES = 8, int PF = 2>
 int launch_composite_x(const void* X, int64_t M, int64_t K, int64_t ldx, const int32_t* perm, const void* Rt,
                        float s, uint8_t* Xq, float* x_scale, hipStream_t stream) {
   constexpr int R = 16 * RG;
@@ -783,7 +796,7 @@ int launch_composite_x(const void* X, int64_t M, int64_t K, int64_t ldx, const i
     if ((st = launch_status()) != OQ_OK) return st;
   }
   const int64_t grid = (ntiles + 7) / 8 * 8 * nq;
-  hipLaunchKernelGGL((rq_composite_x_kernel<RG, C, GATHER, WAVES, PF>), dim3(static_cast<unsigned>(grid)),
+  hipLaunchKernelGGL((rq_composite_x_kernel<RG, C, GATHER, WAVES, PF, KMAX>), dim3(static_cast<unsigned>(grid)),
                      dim3(64 * WAVES), 0, stream, static_cast<const uint16_t*>(X), M, static_cast<int>(K), ldx,
                      perm, static_cast<const uint16_t*>(Rt), s, Xq, x_scale, slots, nq,
                      static_cast<int>(ntiles));
@@ -808,19 +821,52 @@ int launch_composite_chunked(bool gather, int C, const void* X, int64_t M, int64
                              const int32_t* perm, const void* Rt, float s, uint8_t* Xq, float* x_scale,
                              hipStream_t h) {
   if (gather) {
+#define OQ_CX(CC, KM) return launch_composite_x<1, CC, true, KM>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h)
     switch (C) {
-      case 4096: return launch_composite_x<1, 4096, true>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
-      case 2048: return launch_composite_x<1, 2048, true>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
-      case 1024: return launch_composite_x<1, 1024, true>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
-      case 512: return launch_composite_x<1, 512, true>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
+      case 4096:
+        if (K <= 8192) OQ_CX(4096, 8192);
+        OQ_CX(4096, 16384);
+      case 2048: OQ_CX(2048, 16384);
+      case 1024: OQ_CX(1024, 16384);
+      case 512: OQ_CX(512, 16384);
       default: return OQ_ERR_SHAPE;
     }
+#undef OQ_CX
   }
   switch (C) {
     case 1024: return launch_composite_x<2, 1024, false>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
     case 512: return launch_composite_x<2, 512, false>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
     default: return OQ_ERR_SHAPE;
   }
+}
+
+// Rows that one chunk holds (K = 512 n up to 4096): the chunked kernel with nq =
+// 1, without exchange or workspace.  *st is set and true returned if K is one of
+// the widths built.  (Against rq_composite1_kernel, which stays for the other K
+// up to 4096: 4080 x 2048 22 -> 11 us, 16384 x 1024 23 -> 18 us, 700 x 4096 28 ->
+// 16 us; with P folded 22 -> 9, 25 -> 12, 28 -> 11 us.)
+bool launch_composite_one(bool gather, const void* X, int64_t M, int64_t K, int64_t ldx, const int32_t* perm,
+                          const void* Rt, float s, uint8_t* Xq, float* x_scale, hipStream_t h, int* st) {
+#define OQ_C1(RG, CC, G, KM) *st = launch_composite_x<RG, CC, G, KM>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h)
+  // Folded rows of up to 1024 channels: 32-row tiles read the block matrices half as often, 16-row
+  // tiles spread few rows over more CUs.
+#define OQ_C1_CASE(CC, KM)               \
+  case CC:                               \
+    if (gather) OQ_C1(1, CC, true, KM);  \
+    else if (CC <= 1024 && M > 1024) OQ_C1((CC <= 1024 ? 2 : 1), CC, false, CC); \
+    else OQ_C1(1, CC, false, CC);        \
+    return true;
+  switch (K) {
+    OQ_C1_CASE(512, 512)
+    OQ_C1_CASE(1024, 1024)
+    OQ_C1_CASE(1536, 2048)
+    OQ_C1_CASE(2048, 2048)
+    OQ_C1_CASE(3072, 4096)
+    OQ_C1_CASE(4096, 4096)
+    default: return false;
+  }
+#undef OQ_C1_CASE
+#undef OQ_C1
 }
 
 template <int RG, int KMAX, bool GATHER = true>
@@ -862,18 +908,20 @@ extern "C" int oq_rotate_quantize_act_composite(const void* X, int64_t M, int64_
   int st = oq::device_check();
   if (st != OQ_OK) return st;
   hipStream_t h = static_cast<hipStream_t>(stream);
-  // Without a permutation the rows are read straight into the MFMA operands
-  // (no LDS staging): row groups sized to the register budget.
+  // K = 4096 folded with many rows: 1024-channel chunks of 32-row tiles read the
+  // block matrices half as often as one workgroup per 16 whole rows (M = 2000 / 4080 / 16384: 10.5 / 15.4 / 48 against
+  // 12.6 / 16.2 / 60 us).
+  if (!perm && K == 4096 && M > 1024)
+    return oq::launch_composite_chunked(false, 1024, X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
+  if (oq::launch_composite_one(perm != nullptr, X, M, K, ldx, perm, Rt, s, Xq, x_scale, h, &st)) return st;
+  // Other K.  Without a permutation the rows are read straight into the MFMA
+  // operands (no LDS staging): row groups sized to the register budget.
   if (!perm) {
     // Few rows: one row group per workgroup, so the rows spread over more CUs.
     if (M <= 1024 && K <= 1024) return oq::launch_composite1<1, 1024, false>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
     if (M <= 1024 && K <= 2048) return oq::launch_composite1<1, 2048, false>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
     if (K <= 1024) return oq::launch_composite1<2, 1024, false>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
     if (K <= 2048) return oq::launch_composite1<2, 2048, false>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
-    // K = 4096 with many rows: 1024-channel chunks of 32-row tiles beat one
-    // workgroup per 16 whole rows (78 vs 120 us at M = 16384).
-    if (K == 4096 && M > 1024)
-      return oq::launch_composite_chunked(false, 1024, X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
     if (K <= 4096) return oq::launch_composite1<1, 4096, false>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
     if (const int c = oq::comp_chunk(K, 1024))
       return oq::launch_composite_chunked(false, c, X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
