@@ -15,9 +15,9 @@
 // with an arithmetic shift by 8.  A and B take the channels in the same order,
 // so the dot products are unchanged.
 //
-// Two kernels.  M > 64: LDS-staged tiles on v_mfma_i32_32x32x32_i8
-// (gemm_ring.h; the tile by the estimate in gemm_launch).  M <= 64 (and token
-// codes in the 16-row tiled layout): a weight-streaming kernel on
+// Two kernels.  M > 64 (and fewer rows of wide products): LDS-staged tiles on
+// v_mfma_i32_32x32x32_i8 (gemm_ring.h; the tile by the estimate in gemm_launch).
+// Other M <= 64 (and token codes in the 16-row tiled layout): a weight-streaming kernel on
 // v_mfma_i32_16x16x64_i8 with the operands loaded straight into registers
 // (details at gemm_small_kernel).  8-bit token codes (W4A8) use both with
 // the A operand loaded as bytes.
@@ -276,9 +276,15 @@ int launch_small_mb(const GemmArgs& a, hipStream_t stream) {
   // round in the deep cases (1024 threads leave 128 registers per lane).
   constexpr int UBW = A8 ? 2 : 4;
   const dim3 grid(static_cast<unsigned>((a.N + bn - 1) / bn), static_cast<unsigned>((a.M + 16 * MB - 1) / (16 * MB)));
+  // (A round loads UB units per wave whether the wave has them or not, so up to
+  // K = 2048, two units for each of 8 waves and one for each of 16, the rounds
+  // are that short: 5 x 32768 x 2048 11.4 -> 7.1 us.)
   if (wide && shallow) hipLaunchKernelGGL((gemm_small_kernel<EPI, 2, 8, MB, 1, TILED, A8>), grid, dim3(512), 0, stream, a);
+  else if (wide && a.K <= 2048)
+    hipLaunchKernelGGL((gemm_small_kernel<EPI, 2, 8, MB, 2, TILED, A8>), grid, dim3(512), 0, stream, a);
   else if (wide) hipLaunchKernelGGL((gemm_small_kernel<EPI, 2, 8, MB, UBW, TILED, A8>), grid, dim3(512), 0, stream, a);
   else if (shallow) hipLaunchKernelGGL((gemm_small_kernel<EPI, 1, 4, MB, 2, TILED, A8>), grid, dim3(256), 0, stream, a);
+  else if (a.K <= 2048) hipLaunchKernelGGL((gemm_small_kernel<EPI, 1, 16, MB, 1, TILED, A8>), grid, dim3(1024), 0, stream, a);
   else hipLaunchKernelGGL((gemm_small_kernel<EPI, 1, 16, MB, A8 ? 1 : 2, TILED, A8>), grid, dim3(1024), 0, stream, a);
   return launch_status();
 }
@@ -369,9 +375,17 @@ int ring_best(const RingCost (&c)[NT], const GemmArgs& a) {
 int gemm_launch(const GemmArgs& a, Epilogue epi, hipStream_t stream) {
   if (a.M == 0) return OQ_OK;
   // Tiled token codes always take the small-M kernel (row groups of 64 along
-  // grid.y when M > 64); row-layout codes take it up to M = 64.
+  // grid.y when M > 64).  Row-layout codes take it up to M = 16, and up to M = 64
+  // while N <= 8192: its workgroups re-read every token code for 32 columns in
+  // operand order (16 rows of 64 bytes a load), which above one row block costs
+  // more than the weight stream once the columns are many.  M = 40, 32768 x 2048:
+  // 12.8 us against 10.0 on the tiles of the M > 64 product; M = 17, 9000 x 4096: 10.7
+  // against 7.9; M = 64, 10240 x 8192: 27.8 against 14.1; but M = 17, 8192 x 8192:
+  // 11.8 against 13.2; M = 16, 32768 x 4096: 13.8 against 15.4.  Deep and wide W4A4
+  // products go to the tiles at any M (M = 1 / 16, 16384 x 16384: 29 / 32 us against 27 / 25).
   if (a.a_i8 && (epi == EPI_RESID_F32 || epi == EPI_GELU_F16)) return OQ_ERR_ARG;
-  if (a.M <= 64 || a.a_tiled) {
+  const bool deep_wide = !a.a_i8 && a.N >= 16384 && a.K > 8192;
+  if (a.a_tiled || (a.M <= 16 && !deep_wide) || (a.M <= 64 && a.N <= 8192)) {
     switch (epi) {
       case EPI_I32: return launch_small_any<EPI_I32>(a, stream);
       case EPI_F16: return launch_small_any<EPI_F16>(a, stream);
