@@ -219,8 +219,7 @@ int oq_w4a4_gemm_i32_tiled(const uint8_t* Xt, int64_t M, const uint8_t* Wq, int6
  *          then unspecified but every access stays in bounds); or NULL: X is
  *          already in the permuted channel order (P folded into the
  *          producer of X, as U is for the Hadamard path), so (X P) = X and
- *          the rows go straight from global memory into the matrix-core
- *          operands without a gather
+ *          no gather is needed
  * Rt       device fp16 [K/64][64][64], block b column-major:
  *          Rt[b][j][r] = R_b[r][j] (oq_block_rotations_host writes it), 16-byte
  *          aligned.  The products are formed from these fp16 values exactly
@@ -229,8 +228,8 @@ int oq_w4a4_gemm_i32_tiled(const uint8_t* Xt, int64_t M, const uint8_t* Wq, int6
  * Xq       device [M][K/2] codes (16-byte aligned), x_scale device fp32 [M]
  * Device memory: above K = 4096 (and at K = 4096 with perm NULL and M > 1024)
  * the rows are split into channel chunks whose workgroups exchange their
- * partial row maxima through a library-owned device buffer (the inverse
- * permutation and one float per row and chunk), allocated on the first call
+ * partial row maxima through a library-owned device buffer (one float per
+ * row and chunk), allocated on the first call
  * on a GPU, grown when a call needs more and kept until the process ends.
  * Such calls therefore may allocate, and calls that overlap on one GPU (other
  * streams, other host threads) share that buffer and must not run
