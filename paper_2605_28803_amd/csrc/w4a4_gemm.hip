@@ -23,6 +23,7 @@
 // the A operand loaded as bytes.
 #include "common.h"
 #include "gemm_ring.h"
+#include "gemm_rules.h"
 
 namespace oq {
 namespace {
@@ -108,7 +109,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_small_kernel(GemmArgs a) {
   const int64_t m0 = static_cast<int64_t>(blockIdx.y) * ROWS;
   const int64_t Kb = a.K / 2;
   const int nu = static_cast<int>(a.K / 128);
-  const int ubeg = (nu * wave) / WAVES, uend = (nu * (wave + 1)) / WAVES;
+  const int ubeg = small_begin(nu, wave, WAVES), uend = small_begin(nu, wave + 1, WAVES);
 
   // Row-block bases: tiled -> block (m0 / 16 + rb) at unit 0 plus this lane's
   // 16 bytes; rows -> row m0 + 16 rb + lane % 16 at byte 0.  Out-of-range
@@ -133,7 +134,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_small_kernel(GemmArgs a) {
   const uint8_t* bbase[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) bbase[nb] = a.B + min<int64_t>(n0 + nb * 16 + (lane & 15), a.N - 1) * Kb;
-  const int piece = 16 * (lane >> 4);  // this lane's 16 bytes of a 64-byte unit (row layout)
+  const int piece = small_piece(nu, lane >> 4);  // this lane's 16 bytes of a 64-byte unit (row layout)
 
   // Fragments of UB units starting at u0 (a unit past uend reads unit uend - 1
   // or 0 again; its MFMAs are skipped).
@@ -142,7 +143,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_small_kernel(GemmArgs a) {
   auto load_units = [&](int u0) {
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
-      const int uu = u0 + u < uend ? u0 + u : max(uend - 1, 0);
+      const int uu = small_unit(u0 + u, uend);
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) fb[u][nb] = *reinterpret_cast<const uint4*>(bbase[nb] + uu * 64 + piece);
 #pragma unroll
