@@ -1,22 +1,28 @@
-// Index arithmetic of the products that has to hold for every size, in plain
-// C++ (no HIP), so that it can be checked on the host.
+// Rules that choose a product's kernel and its shape, in plain C++ (no HIP), so
+// that they can be checked on the host.
 #pragma once
+
+#include <stdint.h>
 
 namespace oq {
 
-// The few-row product walks K in units of 128 codes (64 packed bytes of a row;
-// 128 bytes of 8-bit codes), nu = K / 128 of them.  Wave `wave` of `waves`
-// takes units [small_begin(wave), small_begin(wave + 1)).
-constexpr int small_begin(int nu, int wave, int waves) { return (nu * wave) / waves; }
-
-// The unit that is loaded where unit u of a wave that ends at uend is asked
-// for: loads are unconditional, and one past the end reads unit uend - 1 or 0
-// again.
-constexpr int small_unit(int u, int uend) { return u < uend ? u : uend > 0 ? uend - 1 : 0; }
-
-// Byte within a unit that a quarter wave reads 16 bytes at (8-bit codes: twice
-// that, 32 bytes).  At K = 64 there is no whole unit: rows hold half of one,
-// and every quarter stays in that half (nothing loaded there is used).
-constexpr int small_piece(int nu, int quarter) { return 16 * (nu > 0 ? quarter : quarter & 1); }
+// Shape of the small-M (weight-streaming) product: 16 nb columns a workgroup
+// of `waves` waves, and ub 128-code units of K that a wave loads a round.
+// 32 columns when N is wide enough to keep more than 256 workgroups busy, else
+// 16; waves sized so that each takes one or two units at K <= 1024, and two
+// (16 columns) or four (32 columns) in a round above; deeper K runs more
+// rounds.  A round loads ub units whether the wave has them or not, so up to K
+// = 2048, two units for each of 8 waves and one for each of 16, the rounds are
+// that short (5 x 32768 x 2048: 11.4 -> 7.1 us), and K = 64, whose rows hold
+// half a unit, loads none and leaves its 64 codes to the last 64-code step.
+// 8-bit token codes take twice the registers per unit: half the units a round
+// in the deep cases (1024 threads leave 128 registers per lane).
+struct SmallShape {
+  int nb, waves, ub;
+};
+constexpr SmallShape small_shape(int64_t N, int64_t K, bool a8) {
+  if (N > 4096) return {2, 8, K < 128 ? 0 : K <= 1024 ? 1 : K <= 2048 || a8 ? 2 : 4};
+  return {1, K <= 1024 ? 4 : 16, K < 128 ? 0 : K <= 1024 ? 2 : K <= 2048 || a8 ? 1 : 2};
+}
 
 }  // namespace oq

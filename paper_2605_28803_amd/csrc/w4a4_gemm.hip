@@ -109,7 +109,7 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_small_kernel(GemmArgs a) {
   const int64_t m0 = static_cast<int64_t>(blockIdx.y) * ROWS;
   const int64_t Kb = a.K / 2;
   const int nu = static_cast<int>(a.K / 128);
-  const int ubeg = small_begin(nu, wave, WAVES), uend = small_begin(nu, wave + 1, WAVES);
+  const int ubeg = (nu * wave) / WAVES, uend = (nu * (wave + 1)) / WAVES;
 
   // Row-block bases: tiled -> block (m0 / 16 + rb) at unit 0 plus this lane's
   // 16 bytes; rows -> row m0 + 16 rb + lane % 16 at byte 0.  Out-of-range
@@ -134,16 +134,16 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_small_kernel(GemmArgs a) {
   const uint8_t* bbase[NB];
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) bbase[nb] = a.B + min<int64_t>(n0 + nb * 16 + (lane & 15), a.N - 1) * Kb;
-  const int piece = small_piece(nu, lane >> 4);  // this lane's 16 bytes of a 64-byte unit (row layout)
+  const int piece = 16 * (lane >> 4);  // this lane's 16 bytes of a 64-byte unit (row layout)
 
   // Fragments of UB units starting at u0 (a unit past uend reads unit uend - 1
   // or 0 again; its MFMAs are skipped).
   constexpr int AH = A8 ? 2 : 1;  // 16-byte A loads per unit and row block
-  uint4 fa[UB][MB][AH], fb[UB][NB];
+  uint4 fa[UB ? UB : 1][MB][AH], fb[UB ? UB : 1][NB];
   auto load_units = [&](int u0) {
 #pragma unroll
     for (int u = 0; u < UB; ++u) {
-      const int uu = small_unit(u0 + u, uend);
+      const int uu = u0 + u < uend ? u0 + u : max(uend - 1, 0);
 #pragma unroll
       for (int nb = 0; nb < NB; ++nb) fb[u][nb] = *reinterpret_cast<const uint4*>(bbase[nb] + uu * 64 + piece);
 #pragma unroll
@@ -218,10 +218,12 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_small_kernel(GemmArgs a) {
   };
   // First round straight-line (the MFMAs of a unit wait only for that unit's
   // loads); deeper K continues in rounds of UB units.
-  mfma_units(ubeg);
-  for (int u0 = ubeg + UB; u0 < uend; u0 += UB) {
-    load_units(u0);
-    mfma_units(u0);
+  if constexpr (UB > 0) {
+    mfma_units(ubeg);
+    for (int u0 = ubeg + UB; u0 < uend; u0 += UB) {
+      load_units(u0);
+      mfma_units(u0);
+    }
   }
   if (!TILED && (a.K & 127) && wave == WAVES - 1) {
     // Final 64 codes: 32 packed bytes per row, 8 per lane.
@@ -263,31 +265,31 @@ __global__ __launch_bounds__(64 * WAVES) void gemm_small_kernel(GemmArgs a) {
   }
 }
 
-// Tile shape of the small-M product: 32 columns per workgroup when N is wide
-// enough to keep more than 256 workgroups busy, else 16; waves sized so that
-// each takes one or two 128-code units of K at K <= 1024 and up to 2 (16
-// columns) or 4 (32 columns) at K <= 4096 in its first round; deeper K runs
-// more rounds.
 template <int EPI, bool TILED, int MB, bool A8 = false>
 int launch_small_mb(const GemmArgs& a, hipStream_t stream) {
-  const bool wide = a.N > 4096;
-  const bool shallow = a.K <= 1024;
-  const int bn = wide ? 32 : 16;
-  // 8-bit token codes take twice the registers per unit: half the units per
-  // round in the deep cases (1024 threads leave 128 registers per lane).
-  constexpr int UBW = A8 ? 2 : 4;
+  const SmallShape sh = small_shape(a.N, a.K, A8);
+  const int bn = 16 * sh.nb;
   const dim3 grid(static_cast<unsigned>((a.N + bn - 1) / bn), static_cast<unsigned>((a.M + 16 * MB - 1) / (16 * MB)));
-  // (A round loads UB units per wave whether the wave has them or not, so up to
-  // K = 2048, two units for each of 8 waves and one for each of 16, the rounds
-  // are that short: 5 x 32768 x 2048 11.4 -> 7.1 us.)
-  if (wide && shallow) hipLaunchKernelGGL((gemm_small_kernel<EPI, 2, 8, MB, 1, TILED, A8>), grid, dim3(512), 0, stream, a);
-  else if (wide && a.K <= 2048)
-    hipLaunchKernelGGL((gemm_small_kernel<EPI, 2, 8, MB, 2, TILED, A8>), grid, dim3(512), 0, stream, a);
-  else if (wide) hipLaunchKernelGGL((gemm_small_kernel<EPI, 2, 8, MB, UBW, TILED, A8>), grid, dim3(512), 0, stream, a);
-  else if (shallow) hipLaunchKernelGGL((gemm_small_kernel<EPI, 1, 4, MB, 2, TILED, A8>), grid, dim3(256), 0, stream, a);
-  else if (a.K <= 2048) hipLaunchKernelGGL((gemm_small_kernel<EPI, 1, 16, MB, 1, TILED, A8>), grid, dim3(1024), 0, stream, a);
-  else hipLaunchKernelGGL((gemm_small_kernel<EPI, 1, 16, MB, A8 ? 1 : 2, TILED, A8>), grid, dim3(1024), 0, stream, a);
-  return launch_status();
+  const dim3 block(64 * sh.waves);
+#define OQ_SMALL(NB, WV, UB)                                                                             \
+  if (sh.nb == NB && sh.waves == WV && sh.ub == UB) {                                                    \
+    hipLaunchKernelGGL((gemm_small_kernel<EPI, NB, WV, MB, UB, TILED, A8>), grid, block, 0, stream, a);  \
+    return launch_status();                                                                              \
+  }
+  if constexpr (!TILED) {  // (the tiled layout has K % 128 == 0)
+    OQ_SMALL(1, 4, 0)
+    OQ_SMALL(2, 8, 0)
+  }
+  OQ_SMALL(1, 4, 2)
+  OQ_SMALL(2, 8, 1)
+  OQ_SMALL(1, 16, 1)
+  OQ_SMALL(2, 8, 2)
+  if constexpr (!A8) {
+    OQ_SMALL(1, 16, 2)
+    OQ_SMALL(2, 8, 4)
+  }
+#undef OQ_SMALL
+  return OQ_ERR_SHAPE;
 }
 
 // Row blocks of 16 (one per workgroup) spread a small-M product over four
@@ -296,9 +298,9 @@ int launch_small_mb(const GemmArgs& a, hipStream_t stream) {
 // 5 thousand waves; not the 8192-column gate|up, whose 32-column workgroups of
 // 8 waves would make 8 thousand).
 bool small_row_blocks_of_16(const GemmArgs& a) {
-  const bool wide = a.N > 4096, shallow = a.K <= 1024;
-  const int64_t bn = wide ? 32 : 16, waves = wide ? 8 : (shallow ? 4 : 16);
-  const int64_t total = (a.N + bn - 1) / bn * ((a.M + 15) / 16) * waves;
+  const SmallShape sh = small_shape(a.N, a.K, false);
+  const int64_t bn = 16 * sh.nb;
+  const int64_t total = (a.N + bn - 1) / bn * ((a.M + 15) / 16) * sh.waves;
   return a.M <= 16 || total <= 4096;
 }
 
