@@ -6,6 +6,42 @@
 
 namespace oq {
 
+// Whether the small-M (weight-streaming) kernel takes a product; the LDS-tiled
+// ring takes the others.  a8: 8-bit token codes; tiled: token codes in the
+// 16-row tiled layout, which only the small-M kernel reads (row groups of 64
+// along grid.y when M > 64).
+//
+// Row-layout codes: up to M = 16, and up to M = 64 while N <= 8192.  A
+// workgroup re-reads every token code for its 32 columns in operand order (16
+// rows of 64 bytes a load), which above one row block costs more than the
+// weight stream once the columns are many.  Weights from HBM, us on the small-M
+// kernel against the ring: 40 x 32768 x 2048 29.2 / 11.6, 17 x 9000 x 4096 13.9 /
+// 11.1, 64 x 10000 x 8192 31.7 / 19.5; 17 x 8192 x 8192 11.8 / 13.2; one row block, 1 and
+// 16 x 16384 x 16384: 29.9 / 37.9 and 34.8 / 39.0 (with weights that stay in the cache
+// the ring is 2 us ahead there).
+// Between 8192 and 16384 columns the ring has at most one 64 x 64 tile per CU,
+// so its time is a tile's whole K, and with few rows the small-M kernel stays
+// ahead where its own K loop is short or the ring's long:
+//  * up to K = 1024, where a wave loads all it needs at once (above, it takes a
+//    second round).  The ring's stages are 512 codes (8-bit tokens: 256), so it
+//    is ahead at a whole number of them: 32 x 8200 x 576 4.1 / 5.1, x 1024 4.6 / 5.1, 48 x
+//    12288 x 576 4.8 / 5.4, x 1024 5.9 / 5.6; W4A8 24 x 12288 x 576 5.2 / 5.5, x 768 5.9 / 5.5,
+//    17 x 8200 x 1024 5.1 / 5.9, 28 x 9000 x 1024 6.2 / 6.0.
+//  * deep K of W4A8, whose tile takes twice the LDS reads: 17 x 8200 x 8192 25.9 /
+//    28.6, 17 x 8200 x 16384 43.4 / 53.3, 28 x 8200 x 16384 49.9 / 53.6, 17 x 16384 x 16384 53.5 /
+//    58.1; but 24 x 9000 x 8192 30.6 / 28.9, 24 x 10000 x 16384 54.8 / 53.6.
+constexpr bool few_rows(int64_t M, int64_t N, int64_t K, bool a8, bool tiled) {
+  if (tiled || M <= 16) return true;
+  if (M > 64 || N > 16384) return false;
+  if (N <= 8192) return true;
+  if (a8) {
+    if (K > 512 && K < 768) return M <= 48;
+    if (K > 768 && K <= 1024) return M <= 24;
+    return (K >= 4096 && N < 9000 && M <= (K > 8192 ? 28 : 24)) || (K > 8192 && M <= 20);
+  }
+  return K > 512 && K <= 1024 && M <= (K < 768 || N < 9000 ? 48 : 36);
+}
+
 // Shape of the small-M (weight-streaming) product: 16 nb columns a workgroup
 // of `waves` waves, and ub 128-code units of K that a wave loads a round.
 // 32 columns when N is wide enough to keep more than 256 workgroups busy, else

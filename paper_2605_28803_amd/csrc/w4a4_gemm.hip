@@ -377,18 +377,8 @@ int ring_best(const RingCost (&c)[NT], const GemmArgs& a) {
 
 int gemm_launch(const GemmArgs& a, Epilogue epi, hipStream_t stream) {
   if (a.M == 0) return OQ_OK;
-  // Tiled token codes always take the small-M kernel (row groups of 64 along
-  // grid.y when M > 64).  Row-layout codes take it up to M = 16, and up to M = 64
-  // while N <= 8192: its workgroups re-read every token code for 32 columns in
-  // operand order (16 rows of 64 bytes a load), which above one row block costs
-  // more than the weight stream once the columns are many.  M = 40, 32768 x 2048:
-  // 12.8 us against 10.0 on the tiles of the M > 64 product; M = 17, 9000 x 4096: 10.7
-  // against 7.9; M = 64, 10240 x 8192: 27.8 against 14.1; but M = 17, 8192 x 8192:
-  // 11.8 against 13.2; M = 16, 32768 x 4096: 13.8 against 15.4.  Deep and wide W4A4
-  // products go to the tiles at any M (M = 1 / 16, 16384 x 16384: 29 / 32 us against 27 / 25).
   if (a.a_i8 && (epi == EPI_RESID_F32 || epi == EPI_GELU_F16)) return OQ_ERR_ARG;
-  const bool deep_wide = !a.a_i8 && a.N >= 16384 && a.K > 8192;
-  if (a.a_tiled || (a.M <= 16 && !deep_wide) || (a.M <= 64 && a.N <= 8192)) {
+  if (few_rows(a.M, a.N, a.K, a.a_i8, a.a_tiled)) {
     switch (epi) {
       case EPI_I32: return launch_small_any<EPI_I32>(a, stream);
       case EPI_F16: return launch_small_any<EPI_F16>(a, stream);

@@ -11,6 +11,7 @@ CSRC = os.path.join(ROOT, "paper_2605_28803_amd", "csrc")
 
 SOURCE = r"""
 #include "gemm_rules.h"
+extern "C" bool few_rows(int64_t M, int64_t N, int64_t K, bool a8, bool tiled) { return oq::few_rows(M, N, K, a8, tiled); }
 extern "C" void small_shape(int64_t N, int64_t K, bool a8, int* out) {
   const oq::SmallShape s = oq::small_shape(N, K, a8);
   out[0] = s.nb, out[1] = s.waves, out[2] = s.ub;
@@ -26,6 +27,8 @@ def rules(tmp_path_factory):
     subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-I", CSRC, str(src), "-o", str(so)], check=True)
     lib = C.CDLL(str(so))
     lib.small_shape.argtypes = [C.c_int64, C.c_int64, C.c_bool, C.POINTER(C.c_int)]
+    lib.few_rows.argtypes = [C.c_int64] * 3 + [C.c_bool] * 2
+    lib.few_rows.restype = C.c_bool
     return lib
 
 
@@ -45,3 +48,35 @@ def test_few_row_loads_stay_within_a_row(rules, N, K, a8):
             unit = u if u < end else max(end - 1, 0)
             assert unit * 64 + 64 <= K // 2
     assert (nb, waves) == ((2, 8) if N > 4096 else (1, 4 if K <= 1024 else 16))
+
+
+# (M, N, K, 8-bit tokens, us on the small-M kernel, us on the ring): both measured on an MI355X in
+# graphs of many calls that rotate through more weights than the caches hold.
+MEASURED = [
+    (1, 16384, 16384, False, 29.9, 37.9), (8, 16384, 16384, False, 32.0, 38.3), (16, 16384, 16384, False, 34.8, 39.0),
+    (17, 8200, 576, False, 4.00, 5.09), (48, 16384, 576, False, 4.96, 5.60), (17, 8200, 1024, False, 4.22, 5.10),
+    (17, 16384, 1024, False, 5.15, 5.90), (32, 8200, 1024, False, 4.59, 5.14), (36, 16384, 768, False, 5.45, 5.61),
+    (40, 8200, 1024, False, 4.81, 5.25), (48, 10000, 1024, False, 5.78, 5.36), (17, 8200, 1088, False, 7.75, 5.97),
+    (17, 32768, 1024, False, 9.06, 7.66), (64, 32768, 512, False, 11.14, 6.20), (17, 9000, 4096, False, 13.9, 11.2),
+    (40, 32768, 2048, False, 29.2, 11.6), (64, 10000, 8192, False, 31.7, 19.5), (17, 8200, 16384, False, 34.9, 31.7),
+    (64, 16384, 16384, False, 60.3, 39.7), (17, 16384, 576, True, 5.07, 5.63), (24, 12288, 576, True, 5.16, 5.53),
+    (24, 12288, 768, True, 5.94, 5.49), (17, 8200, 1024, True, 5.10, 5.87), (24, 16384, 1024, True, 6.36, 6.70),
+    (28, 9000, 1024, True, 6.24, 5.96), (17, 8200, 4096, True, 15.0, 16.1), (17, 8200, 8192, True, 25.9, 28.6),
+    (17, 8200, 16384, True, 43.4, 53.3), (17, 16384, 16384, True, 53.5, 58.1), (20, 12288, 16384, True, 52.8, 54.3),
+    (24, 8200, 8192, True, 27.6, 28.7), (28, 8200, 16384, True, 49.9, 53.6), (24, 9000, 8192, True, 30.6, 28.9),
+    (24, 10000, 16384, True, 54.8, 53.6), (17, 20000, 16384, True, 76.0, 59.4), (40, 32768, 2048, True, 25.0, 12.8),
+    (64, 32768, 8192, True, 92.7, 41.3),
+]
+
+
+@pytest.mark.parametrize("M,N,K,a8,small,ring", MEASURED)
+def test_few_row_rule_takes_the_faster_kernel(rules, M, N, K, a8, small, ring):
+    assert rules.few_rows(M, N, K, a8, False) == (small < ring)
+
+
+def test_few_row_rule_takes_what_only_the_small_kernel_reads(rules):
+    for M in (1, 16, 17, 64, 65, 5000):
+        for N in (8, 8192, 100000):
+            for K in (128, 1024, 16384):
+                assert rules.few_rows(M, N, K, False, True)
+                assert rules.few_rows(M, N, K, False, False) <= (M <= 64)

@@ -33,10 +33,12 @@ W4A4 = [
     (992, 1536, 6528),                     # 64 x 64, four K groups; 384 codes
     (70, 100, 64), (65, 100, 192), (1000, 1544, 576), (300, 520, 320),  # 64 x 64; a single short stage, tails
 ]
-# Few rows: 16 | 17 and 8192 | 8193 columns (the small-M kernel and the 64 x 64 tilings), the deep and wide rule at one
-# row, and the small-M kernel's rounds of one, two and more units per wave (K = 2048 and its neighbours, both widths).
+# Few rows: 16 | 17 and 8192 | 8193 columns (the small-M kernel and the 64 x 64 tilings), one row block deep and wide, and
+# the small-M kernel's rounds of no whole unit (K = 64), one, two and more units per wave (K = 2048 and its neighbours,
+# both widths), and a 20-row product of more than 8192 columns that stays on it (K = 576).
 FEW = [(16, 8256, 1088), (17, 8192, 1088), (17, 8200, 1088), (64, 8200, 4160), (1, 16384, 8256), (16, 16392, 8192),
-       (5, 4100, 2048), (5, 4096, 2048), (16, 4100, 2112), (3, 2560, 2112), (5, 5000, 1984), (40, 5000, 1984)]
+       (5, 4100, 2048), (5, 4096, 2048), (16, 4100, 2112), (3, 2560, 2112), (5, 5000, 1984), (40, 5000, 1984),
+       (1, 100, 64), (50, 4100, 64), (20, 8232, 576)]
 W4A8 = [
     (4000, 4092, 4160),                    # 256 x 256; half a 128-code stage
     (1000, 6100, 1600), (816, 2560, 2112),  # 128 x 128
