@@ -7,8 +7,8 @@
 // is column j and block b's weight rows (the paper's C_in x C_out orientation)
 // are the 64 columns perm[64 b .. 64 b + 63] of W, a 64 x N matrix W_b.
 //
-//  * Channel energies e_j = sum_n W[n][j]^2 in fp64, one workgroup per 16
-//    columns with a fixed reduction order (deterministic, so exactly equal
+//  * Channel energies e_j = sum_n W[n][j]^2 in fp64, one workgroup per 16 to
+//    64 columns with a fixed reduction order (deterministic, so exactly equal
 //    columns get exactly equal energies).
 //  * Zigzag order: the descending rank of e_j (ties to the lower index) by
 //    counting, then the snake deal over the blocks.
@@ -75,35 +75,39 @@ __device__ __forceinline__ uint16_t f64_to_f16_rne(double x) {
   return sign | static_cast<uint16_t>(r);
 }
 
-// e[j] = sum_n W[n][j]^2: 16 columns per workgroup, 64 threads per column
-// (thread g takes rows g, g + 64, ...), their sums added in order.  Bound by
-// the one read of W once the columns are spread over the chip (64 columns per
-// workgroup left 7/8 of it idle: 2560 x 2048 148 us, now 10).
+// e[j] = sum_n W[n][j]^2: CW columns per workgroup, 1024 / CW threads per column
+// (thread g takes rows g, g + 1024 / CW, ...), their sums added in order.  Bound
+// by the one read of W, if the columns are spread over the chip and a row's
+// piece is not so narrow that its cache lines are fetched several times: 2560 x
+// 2048 at 64 / 32 / 16 columns 8.4 / 5.3 / 9.8 us, 2560 x 1024 8.3 / 5.1 / 3.7, 4096 x 4096 14.2 /
+// 12.6 / 22.0, 2048 x 16384 11.0 / 21.4 / 43.0.
+template <int CW>
 __global__ __launch_bounds__(1024) void energy_kernel(const uint16_t* __restrict__ W, int64_t N, int64_t K,
                                                       int64_t ldw, double* __restrict__ e) {
-  __shared__ double part[64][16];
-  const int c = threadIdx.x & 15, g = threadIdx.x >> 4;
-  const int64_t col = static_cast<int64_t>(blockIdx.x) * 16 + c;
+  constexpr int G = 1024 / CW;
+  __shared__ double part[G][CW];
+  const int c = threadIdx.x % CW, g = threadIdx.x / CW;
+  const int64_t col = static_cast<int64_t>(blockIdx.x) * CW + c;
   const bool ok = col < K;
   const uint16_t* wc = W + (ok ? col : 0);
   double acc = 0.0;
   int64_t n = g;
-  for (; n + 7 * 64 < N; n += 8 * 64) {
+  for (; n + 7 * G < N; n += 8 * G) {
     uint16_t w[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) w[u] = wc[(n + 64 * u) * ldw];
+    for (int u = 0; u < 8; ++u) w[u] = wc[(n + G * u) * ldw];
 #pragma unroll
     for (int u = 0; u < 8; ++u) acc = fma(h2d(w[u]), h2d(w[u]), acc);
   }
-  for (; n < N; n += 64) {
+  for (; n < N; n += G) {
     const double a = h2d(wc[n * ldw]);
     acc = fma(a, a, acc);
   }
   part[g][c] = acc;
   __syncthreads();
-  if (threadIdx.x < 16 && ok) {
+  if (threadIdx.x < CW && ok) {
     double s = 0.0;
-    for (int w = 0; w < 64; ++w) s += part[w][c];
+    for (int w = 0; w < G; ++w) s += part[w][c];
     e[col] = s;
   }
 }
@@ -446,8 +450,15 @@ extern "C" int oq_channel_energy(const void* W, int64_t N, int64_t K, int64_t ld
   if (!oq::aligned(W, 2) || !oq::aligned(energy, 8)) return OQ_ERR_ALIGN;
   int st = oq::device_check();
   if (st != OQ_OK) return st;
-  hipLaunchKernelGGL(oq::energy_kernel, dim3(static_cast<unsigned>((K + 15) / 16)), dim3(1024), 0,
-                     static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(W), N, K, ldw, energy);
+  hipStream_t h = static_cast<hipStream_t>(stream);
+  const uint16_t* w = static_cast<const uint16_t*>(W);
+#define OQ_ENERGY(CW) \
+  hipLaunchKernelGGL(oq::energy_kernel<CW>, dim3(static_cast<unsigned>((K + CW - 1) / CW)), dim3(1024), 0, h, w, N, K, ldw, energy)
+  // The widest piece that still gives about a hundred workgroups.
+  if (K >= 6144) OQ_ENERGY(64);
+  else if (K >= 2048) OQ_ENERGY(32);
+  else OQ_ENERGY(16);
+#undef OQ_ENERGY
   return oq::launch_status();
 }
 

@@ -1,0 +1,30 @@
+"""The weight preparation at the widths where its kernels change (GPU): the channel
+energies' column split (16, 32 and 64 columns a workgroup: K below and at 2048 and 6144),
+with ragged columns and row counts around a round of a workgroup's rows."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2605_28803_amd as oq
+from oracle import composite
+from tests.test_gpu_prepare import _weight
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+EPS = 2.0 ** -52
+
+
+@pytest.mark.parametrize("N,K", [(511, 2040), (512, 2047), (33, 2048), (257, 2049), (1, 6143), (129, 6144), (130, 6150)])
+def test_channel_energy_column_split(N, K):
+    """fp64 sums in another order (within N * 2^-52 relative); equal columns have equal energies bit for bit, wherever
+    they lie in a workgroup."""
+    print(f"channel_energy N={N} K={K}", flush=True)
+    w16 = _weight(6300 + N + K, N, K)
+    for j in (1, 15, 16, 31, 63, 64, K - 1):
+        w16[:, j] = w16[:, 0]
+    wide = torch.zeros((N, K + 3), dtype=torch.float16, device=DEV)
+    wide[:, :K] = torch.from_numpy(w16).to(DEV)
+    e = oq.channel_energy(wide[:, :K]).cpu().numpy()
+    ref = composite.channel_energy(w16.astype(np.float64))
+    assert np.all(np.abs(e - ref) <= 2 * N * EPS * ref)
+    assert np.all(e[[1, 15, 16, 31, 63, 64, K - 1]] == e[0])
