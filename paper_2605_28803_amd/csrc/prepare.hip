@@ -152,24 +152,34 @@ __global__ __launch_bounds__(1024) void zigzag_kernel(const double* __restrict__
 
 // G_b = W_b W_b^T in fp64 on v_mfma_f64_16x16x4 (lane l holds row k = l / 16 of
 // W_b^T, column l % 16, for either operand; element i of the result is row
-// 4 i + l / 16, column l % 16).  The ten 16 x 16 tiles on and above the
-// diagonal go to six workgroups, each with at most two groups of 16 columns to
-// gather: (0,0)(0,1), (1,1)(1,2), (2,2)(2,3), (3,3)(3,0), (0,2), (1,3).  Its 8
-// waves take four rows in turn each; their sums are added in order.  Bound by
-// the gather (2-byte loads of permuted columns).
-__global__ __launch_bounds__(512) void gram_kernel(const uint16_t* __restrict__ W, int64_t N, int64_t K, int64_t ldw,
-                                                   const int32_t* __restrict__ perm, double* __restrict__ G) {
+// 4 i + l / 16, column l % 16): the ten 16 x 16 tiles on and above the diagonal.
+// The waves take four rows in turn each; their sums are added in order.  Bound
+// by the gather (2-byte loads of permuted columns: each touches a cache line of
+// its own, which other blocks want at about the same time), so by the number of
+// gathers while there are few blocks to spread over the chip, and by how much
+// of the weight is in flight, and stays in L2, when there are many.
+//
+// gram_split_kernel: the tiles of a block on six workgroups, each with at most
+// two groups of 16 columns to gather: (0,0)(0,1), (1,1)(1,2), (2,2)(2,3),
+// (3,3)(3,0), (0,2), (1,3).  Three gathers of the weight in all.
+// gram_kernel: one workgroup per block, one gather.
+// us, six workgroups / one: 2560 x 1024 29 / 87, 2560 x 2048 49 / 93, 1024 x 3072 57 / 45,
+// 4096 x 4096 325 / 171, 8192 x 8192 2314 / 421, 2048 x 16384 1166 / 134.
+__device__ __forceinline__ int gram_column(const int32_t* perm, int b, int g, int lane, int64_t K) {
+  const int32_t c = perm[b * kB + 16 * g + (lane & 15)];  // clamped: an out-of-range entry cannot address outside the row
+  return c < 0 ? 0 : (c >= K ? static_cast<int>(K - 1) : c);
+}
+
+__global__ __launch_bounds__(512) void gram_split_kernel(const uint16_t* __restrict__ W, int64_t N, int64_t K,
+                                                         int64_t ldw, const int32_t* __restrict__ perm,
+                                                         double* __restrict__ G) {
   __shared__ double red[8][2][256];
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int b = blockIdx.x / 6, t = blockIdx.x % 6;
   const int g0 = t < 4 ? t : t - 4, g1 = t < 4 ? (t + 1) & 3 : t - 2;
   const bool two = t < 4;  // the diagonal tile (g0, g0) as well
-  auto column = [&](int g) {  // clamped: an out-of-range entry cannot address outside the row
-    const int32_t c = perm[b * kB + 16 * g + (lane & 15)];
-    return c < 0 ? 0 : (c >= K ? static_cast<int>(K - 1) : c);
-  };
   const int kr = lane >> 4;
-  const uint16_t *w0 = W + column(g0), *w1 = W + column(g1);
+  const uint16_t *w0 = W + gram_column(perm, b, g0, lane, K), *w1 = W + gram_column(perm, b, g1, lane, K);
   v4d d = {0, 0, 0, 0}, x = {0, 0, 0, 0};
   constexpr int UN = 8;
   for (int64_t n0 = 4 * wv; n0 < N; n0 += 32 * UN) {
@@ -202,6 +212,61 @@ __global__ __launch_bounds__(512) void gram_kernel(const uint16_t* __restrict__ 
   double* g = G + static_cast<int64_t>(b) * kB * kB;
   g[i * kB + j] = s;
   if (!which) g[j * kB + i] = s;
+}
+
+__global__ __launch_bounds__(256) void gram_kernel(const uint16_t* __restrict__ W, int64_t N, int64_t K, int64_t ldw,
+                                                   const int32_t* __restrict__ perm, double* __restrict__ G) {
+  constexpr int WV = 4, UN = 4;
+  __shared__ double red[WV][256];
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int b = blockIdx.x, kr = lane >> 4;
+  const uint16_t* w[4];
+#pragma unroll
+  for (int g = 0; g < 4; ++g) w[g] = W + gram_column(perm, b, g, lane, K);
+  v4d x[4][4];  // (on and above the diagonal)
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int f = g; f < 4; ++f) x[g][f] = v4d{0, 0, 0, 0};
+  for (int64_t n0 = 4 * wv; n0 < N; n0 += 4 * WV * UN) {
+    uint16_t a[UN][4];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int64_t n = n0 + 4 * WV * u + kr, nc = n < N ? n : N - 1;  // clamped row; its values are replaced by 0
+#pragma unroll
+      for (int g = 0; g < 4; ++g) {
+        a[u][g] = w[g][nc * ldw];
+        if (n >= N) a[u][g] = 0;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      double v[4];
+#pragma unroll
+      for (int g = 0; g < 4; ++g) v[g] = h2d(a[u][g]);
+#pragma unroll
+      for (int g = 0; g < 4; ++g)
+#pragma unroll
+        for (int f = g; f < 4; ++f) x[g][f] = __builtin_amdgcn_mfma_f64_16x16x4f64(v[g], v[f], x[g][f], 0, 0, 0);
+    }
+  }
+  double* gb = G + static_cast<int64_t>(b) * kB * kB;
+  const int el = threadIdx.x;
+#pragma unroll
+  for (int g = 0; g < 4; ++g)
+#pragma unroll
+    for (int f = g; f < 4; ++f) {
+      __syncthreads();  // (the last tile's sums are read)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) red[wv][(4 * i + kr) * 16 + (lane & 15)] = x[g][f][i];
+      __syncthreads();
+      double s = 0.0;
+#pragma unroll
+      for (int v = 0; v < WV; ++v) s += red[v][el];
+      const int i = 16 * g + el / 16, j = 16 * f + el % 16;
+      gb[i * kB + j] = s;
+      if (g != f) gb[j * kB + i] = s;
+    }
 }
 
 // The round-robin order: at step k (mod 63) slot m of 32 holds the pair (p, q) =
@@ -483,10 +548,12 @@ extern "C" int oq_block_svd(const void* W, int64_t N, int64_t K, int64_t ldw, co
   if (!oq::aligned(perm, 4) || !oq::aligned(U, 8) || !oq::aligned(sigma2, 8)) return OQ_ERR_ALIGN;
   if ((st = oq::device_check()) != OQ_OK) return st;
   // (U holds the Gram matrices in between.)
-  hipLaunchKernelGGL(oq::gram_kernel, dim3(static_cast<unsigned>(6 * (K / oq::kB))), dim3(512), 0,
-                     static_cast<hipStream_t>(stream), static_cast<const uint16_t*>(W), N, K, ldw, perm, U);
-  hipLaunchKernelGGL(oq::block_eig_kernel, dim3(static_cast<unsigned>(K / oq::kB)), dim3(896), 0,
-                     static_cast<hipStream_t>(stream), U, sigma2);
+  hipStream_t h = static_cast<hipStream_t>(stream);
+  const uint16_t* w = static_cast<const uint16_t*>(W);
+  const unsigned nb = static_cast<unsigned>(K / oq::kB);
+  if (nb > 32) hipLaunchKernelGGL(oq::gram_kernel, dim3(nb), dim3(256), 0, h, w, N, K, ldw, perm, U);
+  else hipLaunchKernelGGL(oq::gram_split_kernel, dim3(6 * nb), dim3(512), 0, h, w, N, K, ldw, perm, U);
+  hipLaunchKernelGGL(oq::block_eig_kernel, dim3(nb), dim3(896), 0, h, U, sigma2);
   return oq::launch_status();
 }
 

@@ -1,6 +1,7 @@
 """The weight preparation at the widths where its kernels change (GPU): the channel
 energies' column split (16, 32 and 64 columns a workgroup: K below and at 2048 and 6144),
-with ragged columns and row counts around a round of a workgroup's rows."""
+with ragged columns and row counts around a round of a workgroup's rows, and the Gram
+matrices' split (six workgroups a block up to K = 2048, one above)."""
 import numpy as np
 import pytest
 import torch
@@ -28,3 +29,21 @@ def test_channel_energy_column_split(N, K):
     ref = composite.channel_energy(w16.astype(np.float64))
     assert np.all(np.abs(e - ref) <= 2 * N * EPS * ref)
     assert np.all(e[[1, 15, 16, 31, 63, 64, K - 1]] == e[0])
+
+
+@pytest.mark.parametrize("N,K", [(1, 2048), (257, 2048), (1, 2112), (63, 2112), (65, 3072), (1025, 4096)])
+def test_block_svd_gram_split(N, K):
+    """U_b diag(sigma_b^2) U_b^T is the block's Gram matrix.  The fp64 products are exact and their N-term sums within
+    N * 2^-53 of sum |w_i w_j|; the eigendecomposition's backward error is a few hundred roundings (64 sweeps of pairs)
+    of the matrix's norm."""
+    print(f"block_svd N={N} K={K}", flush=True)
+    w16 = _weight(6400 + N + K, N, K)
+    perm = np.random.default_rng(K).permutation(K).astype(np.int32)
+    wide = torch.full((N, K + 5), 9.0, dtype=torch.float16, device=DEV)
+    wide[:, :K] = torch.from_numpy(w16).to(DEV)
+    U, lam = oq.block_svd(wide[:, :K], torch.from_numpy(perm).to(DEV))
+    U, lam = U.cpu().numpy(), lam.cpu().numpy()
+    wb = w16.astype(np.float64)[:, perm].reshape(N, K // 64, 64)
+    for b in range(K // 64):
+        G = wb[:, b].T @ wb[:, b]
+        assert np.linalg.norm((U[b] * lam[b]) @ U[b].T - G) <= (N + 640) * EPS * np.trace(G)
