@@ -331,8 +331,9 @@ __global__ __launch_bounds__(896) void block_eig_kernel(double* __restrict__ GU,
   // |a_pq| <= 2^-53 sqrt(|a_pp a_qq|), or at the rounding level of the whole
   // matrix, |a_pq| <= 2^-52 trace(G) (entries of a numerically null eigenspace
   // would otherwise keep rotating among themselves).  The angle needs no last
-  // bit; c^2 + s^2 = 1 does, so c takes two Newton steps.  Returns whether any
-  // pair rotates.
+  // bit, since what it leaves of the pair stays in the matrix (the hardware's
+  // reciprocals and one Newton step give a few ulp); c^2 + s^2 = 1 does, so c
+  // takes two Newton steps.  Returns whether any pair rotates.
   auto next_rotations = [&](int x, int k) -> bool {
     // Slots that hold the coming pair now: its top comes from the top of slot
     // m + 1 (slot 31: its own bottom), its bottom from the bottom of slot m - 1
@@ -413,12 +414,10 @@ __global__ __launch_bounds__(896) void block_eig_kernel(double* __restrict__ GU,
         const double f00 = r2[i].x * e00[i] - r2[i].y * e01[i], f01 = r2[i].y * e00[i] + r2[i].x * e01[i];
         const double f10 = r2[i].x * e10[i] - r2[i].y * e11[i], f11 = r2[i].y * e10[i] + r2[i].x * e11[i];
         const double h00 = r1.x * f00 - r1.y * f10, h11 = r1.y * f01 + r1.x * f11;
-        double h01 = r1.x * f01 - r1.y * f11, h10 = r1.y * f00 + r1.x * f10;
-        // In a slot's own block the rotated pair becomes exactly 0, and both off-diagonal entries one value.
-        if (dist == 0) {
-          if (r1.y != 0.0) h01 = 0.0;
-          h10 = h01;
-        }
+        const double h01 = r1.x * f01 - r1.y * f11;
+        double h10 = r1.y * f00 + r1.x * f10;
+        // In a slot's own block both off-diagonal entries are one value, what the rotation left of the pair.
+        if (dist == 0) h10 = h01;
         if (dist < 16 || (dist == 16 && m < 16)) {
           A[x ^ 1][p1][p2[i]] = h00;
           A[x ^ 1][p1][q2[i]] = h01;

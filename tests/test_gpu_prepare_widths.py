@@ -1,7 +1,8 @@
 """The weight preparation at the widths where its kernels change (GPU): the channel
 energies' column split (16, 32 and 64 columns a workgroup: K below and at 2048 and 6144),
 with ragged columns and row counts around a round of a workgroup's rows, and the Gram
-matrices' split (six workgroups a block up to K = 2048, one above)."""
+matrices' split (six workgroups a block up to K = 2048, one above); and the
+precision of a single Jacobi rotation."""
 import numpy as np
 import pytest
 import torch
@@ -47,3 +48,25 @@ def test_block_svd_gram_split(N, K):
     for b in range(K // 64):
         G = wb[:, b].T @ wb[:, b]
         assert np.linalg.norm((U[b] * lam[b]) @ U[b].T - G) <= (N + 640) * EPS * np.trace(G)
+
+
+@pytest.mark.parametrize("seed,spread", [(0, 0.0), (1, 0.0), (2, 2.0), (3, 4.0)])
+def test_block_svd_single_rotations(seed, spread):
+    """A block whose channels overlap only in pairs takes one rotation a pair, so its angle's own error shows.  A
+    vector of a 2 x 2 block G is good to a few roundings: |G v - (v G v) v| <= 8 * 2^-53 |G| |v| (angle, sine and cosine,
+    one product each, all within 2 ulp).  An angle of 2^-46 whose remainder is dropped leaves 100 times that."""
+    rng = np.random.default_rng(6500 + seed)
+    w16 = np.zeros((64, 64), np.float16)
+    order = rng.permutation(64)
+    for i in range(32):
+        w16[2 * i:2 * i + 2, order[2 * i:2 * i + 2]] = rng.standard_normal((2, 2)) * 2.0 ** rng.uniform(-spread, spread)
+    U, lam = oq.block_svd(torch.from_numpy(w16).to(DEV), torch.arange(64, dtype=torch.int32, device=DEV))
+    U, lam = U.cpu().numpy()[0].astype(np.longdouble), lam.cpu().numpy()[0]
+    w = w16.astype(np.longdouble)
+    G = w.T @ w
+    for i in range(64):
+        v = U[:, i]
+        assert np.count_nonzero(v) <= 2
+        scale = np.linalg.norm((np.abs(G) @ np.abs(v)).astype(np.float64))
+        assert np.linalg.norm((G @ v - (v @ G @ v) * v).astype(np.float64)) <= 8 * 2.0 ** -53 * scale
+        assert abs(float(v @ G @ v) - lam[i]) <= 16 * 2.0 ** -53 * scale
