@@ -28,7 +28,6 @@
 // the only rounding of the transform.  Rows past RW in a fragment are zero.
 #include <algorithm>
 #include <cmath>
-#include <mutex>
 
 #include "common.h"
 #include "rq_device.h"
@@ -443,11 +442,9 @@ __global__ __launch_bounds__(512) void rq_composite1_kernel(const uint16_t* __re
 // folded): the permuted channels of a row are cut into nq = K / C chunks of C
 // channels, and each (tile of R = 16 RG rows, chunk) pair is one workgroup, so
 // that each block matrix R_b is read once per R rows instead of once per few
-// rows.  The nq workgroups of a
-// tile exchange their rows' partial maxima through per-launch slots in global
-// memory (initialised to -1 by comp_slots_kernel; a published maximum is >= 0)
-// and each quantizes its own chunk, so every y value is computed once and
-// stays in registers.
+// rows.  The nq workgroups of a tile exchange their rows' partial maxima and
+// each quantizes its own chunk, so every y value is computed once and stays in
+// registers.
 //
 // Staging with the online permutation: a row at a time goes through registers
 // (16-byte loads, four rows ahead) into a raw LDS row, from which each thread
@@ -458,16 +455,25 @@ __global__ __launch_bounds__(512) void rq_composite1_kernel(const uint16_t* __re
 // storing from registers the channels that fall into the chunk under a mask
 // keeps 1 / nq of the store lanes at work (4080 x 16384: 166 us); loading them
 // from global memory 2 bytes each in source order runs at one lane per clock
-// (120 us); this, with the block matrices and the packing below, takes 84 us.  At C = 4096 and K = 16384 the two buffers are
-// all of the LDS, so the chunk's rows are not padded: 16-byte piece p of row r
-// is stored at p ^ r, which spreads the operand reads of 16 rows over the banks.
-// Without a permutation the chunk's columns are copied directly into padded rows.
+// (120 us); this, with the block matrices and the packing below, takes 84 us.
+// At C = 4096 and K = 16384 the two buffers are all of the LDS, so the chunk's
+// rows are not padded: 16-byte piece p of row r is stored at p ^ r, which
+// spreads the operand reads of 16 rows over the banks.  Without a permutation
+// the chunk's columns are copied directly to the same places.
 //
-// Exchange: the tile's workgroups are dispatched together (ids x + 8 (nq t' +
+// Exchange: through the call's own output, so that any number of calls may run
+// at once.  Until chunk q stores its codes, its part of the tile's first row of
+// Xq carries the maxima of the tile's R rows and, behind them, the nq chunks'
+// acknowledgements (together in a few cache lines: a word in each row instead
+// took up to 40% longer).  comp_words_kernel sets
+// them all to kWait (sign bit set; a maximum is >= 0).  A workgroup publishes
+// its maxima, waits for every chunk's, acknowledges to the others that it has
+// read them, and stores its codes over the words once all the others have
+// acknowledged.  The tile's workgroups are dispatched together (ids x + 8 (nq t' +
 // q) for XCD x), so a workgroup only waits for partners dispatched at the same
-// time.  The wait polls with agent-scope atomic loads and is bounded; if the
-// bound is ever reached the tile's token scales are written as NaN (never a
-// silent result) and the workgroup finishes, so the grid always drains.
+// time.  The waits poll with agent-scope atomic loads and are bounded, and a
+// workgroup that gives up goes on without storing codes, so the grid always
+// drains.
 // ---------------------------------------------------------------------------
 constexpr int kPollLimit = 1 << 20;
 
@@ -479,17 +485,34 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-__global__ __launch_bounds__(1024) void comp_slots_kernel(float* __restrict__ slots, int64_t nslots) {
-  for (int64_t i = static_cast<int64_t>(blockIdx.x) * 1024 + threadIdx.x; i < nslots;
-       i += static_cast<int64_t>(gridDim.x) * 1024)
-    slots[i] = -1.0f;
+constexpr uint32_t kWait = 0xFFFFFFFFu;
+
+// Word w of chunk p's part of a row of codes (C / 8 words).
+__device__ __forceinline__ uint32_t* exchange_word(uint8_t* Xq, int64_t row, int K, int C, int p, int w) {
+  return reinterpret_cast<uint32_t*>(Xq + row * (K / 2) + p * (C / 2)) + w;
+}
+// Waits until a word is no longer kWait, for at most `limit` polls.
+__device__ __forceinline__ uint32_t exchange_wait(const uint32_t* w, int limit) {
+  uint32_t v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int it = 0; (v >> 31) && it < limit; ++it) {
+    __builtin_amdgcn_s_sleep(2);
+    v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  return v;
+}
+
+// n = nq (R + nq) words per tile.
+__global__ __launch_bounds__(256) void comp_words_kernel(uint8_t* __restrict__ Xq, int ntiles, int K, int C, int nq, int R) {
+  const int per = R + nq, n = nq * per;
+  const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x, tile = i / n;
+  const int in = static_cast<int>(i - tile * n);
+  if (tile < ntiles) *exchange_word(Xq, tile * R, K, C, in / per, in % per) = kWait;
 }
 
 template <int RG, int C, bool GATHER, int WAVES, int PF, int KMAX>
 __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
     const uint16_t* __restrict__ X, int64_t M, int K, int64_t ldx, const int32_t* __restrict__ perm,
-    const uint16_t* __restrict__ Rt, float s_t, uint8_t* __restrict__ Xq, float* __restrict__ xs,
-    float* __restrict__ slots, int nq, int ntiles) {
+    const uint16_t* __restrict__ Rt, float s_t, uint8_t* __restrict__ Xq, float* __restrict__ xs, int nq, int ntiles) {
   constexpr int NT = 64 * WAVES;
   constexpr int R = 16 * RG, XS = C;
   constexpr int NBC = C / kCB, NBW = NBC / WAVES;  // blocks per chunk, per wave
@@ -501,12 +524,15 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
   constexpr int RPS = KMAX >= 1024 ? 16384 / KMAX : 16;
   constexpr int AUXB = GATHER && RPS * KMAX * 2 > WAVES * 2048 ? RPS * KMAX * 2 : WAVES * 2048;
   __shared__ __attribute__((aligned(16))) uint8_t smem[R * XS * 2 + AUXB];
-  static_assert((WAVES * R + R + 1) * 4 <= AUXB && WAVES * 2048 <= AUXB, "auxiliary region");
+  constexpr int NQMAX = 16384 / C;
+  static_assert((WAVES * R + R + NQMAX * R + 1) * 4 <= AUXB && WAVES * 2048 <= AUXB, "auxiliary region");
+  static_assert(R + NQMAX <= C / 8, "exchange words");
   uint16_t* sx = reinterpret_cast<uint16_t*>(smem);
   uint16_t* raw = sx + R * XS;
   float (*red)[R] = reinterpret_cast<float (*)[R]>(raw);
   float* gscale = reinterpret_cast<float*>(raw) + WAVES * R;
-  int& timed_out = *reinterpret_cast<int*>(gscale + R);
+  float* pmax = gscale + R;  // [nq][R] the chunks' maxima
+  int& timed_out = *reinterpret_cast<int*>(pmax + NQMAX * R);
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int xcd = blockIdx.x % 8, idx = blockIdx.x / 8;
@@ -667,33 +693,32 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
       if (r16 == 0) red[wave][rg * 16 + 4 * qq + e] = m;
     }
   __syncthreads();  // also: every wave's reads of sx are done (sx is reused for the codes)
-  float* tslots = slots + static_cast<int64_t>(tile) * nq * R;  // [nq][R] of this tile
   if (tid < R) {
     float m = red[0][tid];
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) m = fmaxf(m, red[w][tid]);
-    if (nq == 1) {
-      red[0][tid] = m;
-    } else {
-      __hip_atomic_store(&tslots[q * R + tid], m, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    red[0][tid] = m;
+    if (nq > 1)
+      __hip_atomic_store(exchange_word(Xq, row0, K, C, q, tid), __float_as_uint(m), __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_AGENT);
   }
   if (nq > 1) {
     // Thread t < nq R waits for partner t / R's maximum of row t % R (its own
     // chunk's included).
     for (int t = tid; t < nq * R; t += NT) {
-      float v = __hip_atomic_load(&tslots[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      for (int it = 0; !(v >= 0.0f) && it < kPollLimit; ++it) {
-        __builtin_amdgcn_s_sleep(2);
-        v = __hip_atomic_load(&tslots[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      uint32_t v = exchange_wait(exchange_word(Xq, row0, K, C, t / R, t % R), kPollLimit);
+      if (v >> 31) {
+        timed_out = 1;
+        v = 0;
       }
-      if (!(v >= 0.0f)) timed_out = 1;
+      pmax[t] = __uint_as_float(v);
     }
     __syncthreads();
+    if (tid < nq && tid != q)
+      __hip_atomic_store(exchange_word(Xq, row0, K, C, tid, R + q), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     if (tid < R) {
       float m = 0.0f;
-      for (int p = 0; p < nq; ++p)
-        m = fmaxf(m, __hip_atomic_load(&tslots[p * R + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+      for (int p = 0; p < nq; ++p) m = fmaxf(m, pmax[p * R + tid]);
       red[0][tid] = m;
     }
   }
@@ -703,7 +728,7 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
     const float a_z = m * s_t;
     const float delta = a_z / 7.0f;
     gscale[tid] = delta > 0.0f ? s_t / delta : 0.0f;
-    if (q == 0 && row0 + tid < M) xs[row0 + tid] = timed_out ? __builtin_nanf("") : delta / s_t;
+    red[1][tid] = delta / s_t;
   }
   __syncthreads();
 
@@ -737,7 +762,12 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
           scodes[(rg * 16 + crow) * (C / 8) + ((wb0 + i) * kCB + cb * 16 + (r16 & 8)) / 8] = d;
       }
   }
+  if (nq > 1 && tid < nq && tid != q)  // (the other chunks have read this one's maxima)
+    if (exchange_wait(exchange_word(Xq, row0, K, C, q, R + tid), kPollLimit) >> 31) timed_out = 1;
   __syncthreads();
+  const bool failed = timed_out;
+  if (q == 0 && tid < R && row0 + tid < M) xs[row0 + tid] = failed ? __builtin_nanf("") : red[1][tid];
+  if (failed) return;
   constexpr int CPR = C / 32;  // 16-byte code pieces per row of the chunk
   for (int p = tid; p < R * CPR; p += NT) {
     const int r = p / CPR, c16 = p % CPR;
@@ -747,36 +777,6 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
   }
 }
 
-// Device workspace of the chunked kernel (the exchange slots), one per GPU, grown on demand and kept for the process.
-struct CompWork {
-  void* ptr = nullptr;
-  size_t bytes = 0;
-};
-constexpr int kMaxDevices = 64;
-CompWork g_comp_work[kMaxDevices];
-std::mutex g_comp_mu;
-
-int comp_workspace(size_t bytes, void** out) {
-  int dev = 0;
-  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return OQ_ERR_HIP;
-  std::lock_guard<std::mutex> lock(g_comp_mu);
-  CompWork& w = g_comp_work[dev];
-  if (w.bytes < bytes) {
-    // hipFree waits for the device, so no launch still uses the old buffer.
-    if (w.ptr && hipFree(w.ptr) != hipSuccess) return OQ_ERR_HIP;
-    w.ptr = nullptr;
-    w.bytes = 0;
-    const size_t grow = bytes + bytes / 2;
-    if (hipMalloc(&w.ptr, grow) != hipSuccess) {
-      w.ptr = nullptr;
-      return OQ_ERR_HIP;
-    }
-    w.bytes = grow;
-  }
-  *out = w.ptr;
-  return OQ_OK;
-}
-
 template <int RG, int C, bool GATHER, int KMAX = C, int WAVES = 8, int PF = 2>
 int launch_composite_x(const void* X, int64_t M, int64_t K, int64_t ldx, const int32_t* perm, const void* Rt,
                        float s, uint8_t* Xq, float* x_scale, hipStream_t stream) {
@@ -784,22 +784,17 @@ int launch_composite_x(const void* X, int64_t M, int64_t K, int64_t ldx, const i
   const int64_t ntiles = (M + R - 1) / R;
   const int nq = static_cast<int>(K / C);
   if (ntiles > (int64_t{1} << 26)) return OQ_ERR_SHAPE;
-  const int64_t nslots = nq > 1 ? ntiles * nq * R : 0;
-  float* slots = nullptr;
-  if (nslots > 0) {
-    void* ws = nullptr;
-    int st = comp_workspace(static_cast<size_t>(nslots) * 4, &ws);
+  if (nq > 1) {
+    const int64_t words = ntiles * nq * (R + nq);
+    hipLaunchKernelGGL(comp_words_kernel, dim3(static_cast<unsigned>((words + 255) / 256)), dim3(256), 0, stream, Xq,
+                       static_cast<int>(ntiles), static_cast<int>(K), C, nq, R);
+    const int st = launch_status();
     if (st != OQ_OK) return st;
-    slots = static_cast<float*>(ws);
-    const int64_t nwg = std::min<int64_t>((nslots + 1023) / 1024, 256);
-    hipLaunchKernelGGL(comp_slots_kernel, dim3(static_cast<unsigned>(nwg)), dim3(1024), 0, stream, slots, nslots);
-    if ((st = launch_status()) != OQ_OK) return st;
   }
   const int64_t grid = (ntiles + 7) / 8 * 8 * nq;
   hipLaunchKernelGGL((rq_composite_x_kernel<RG, C, GATHER, WAVES, PF, KMAX>), dim3(static_cast<unsigned>(grid)),
                      dim3(64 * WAVES), 0, stream, static_cast<const uint16_t*>(X), M, static_cast<int>(K), ldx,
-                     perm, static_cast<const uint16_t*>(Rt), s, Xq, x_scale, slots, nq,
-                     static_cast<int>(ntiles));
+                     perm, static_cast<const uint16_t*>(Rt), s, Xq, x_scale, nq, static_cast<int>(ntiles));
   return launch_status();
 }
 
