@@ -473,7 +473,11 @@ __global__ __launch_bounds__(512) void rq_composite1_kernel(const uint16_t* __re
 // q) for XCD x), so a workgroup only waits for partners dispatched at the same
 // time.  The waits poll with agent-scope atomic loads and are bounded, and a
 // workgroup that gives up goes on without storing codes, so the grid always
-// drains.
+// drains.  The token scales are formed by atomic maximum over the bits, from 0:
+// chunk 0 gives the scale, any chunk that gives up a NaN, which is above every
+// number, so no order of the two hides it.  (Chunk 0 waiting for a word from
+// every other took 0.7 us more.)  give_up: the chunk that gives up at once on the maxima (chunk p: p) or
+// on the acknowledgements (nq + p); -1 but in a test.
 // ---------------------------------------------------------------------------
 constexpr int kPollLimit = 1 << 20;
 
@@ -485,26 +489,32 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
-constexpr uint32_t kWait = 0xFFFFFFFFu;
+constexpr uint32_t kWait = 0xFFFFFFFFu, kNaN = 0x7FC00000u;
 
 // Word w of chunk p's part of a row of codes (C / 8 words).
 __device__ __forceinline__ uint32_t* exchange_word(uint8_t* Xq, int64_t row, int K, int C, int p, int w) {
   return reinterpret_cast<uint32_t*>(Xq + row * (K / 2) + p * (C / 2)) + w;
 }
-// Waits until a word is no longer kWait, for at most `limit` polls.
-__device__ __forceinline__ uint32_t exchange_wait(const uint32_t* w, int limit) {
+__device__ __forceinline__ void exchange_store(uint32_t* w, uint32_t v) {
+  __hip_atomic_store(w, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+// Waits until a word is no longer kWait, for at most kPollLimit polls.
+__device__ __forceinline__ uint32_t exchange_wait(const uint32_t* w, bool give_up) {
+  if (give_up) return kWait;
   uint32_t v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  for (int it = 0; (v >> 31) && it < limit; ++it) {
+  for (int it = 0; (v >> 31) && it < kPollLimit; ++it) {
     __builtin_amdgcn_s_sleep(2);
     v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   return v;
 }
 
-// n = nq (R + nq) words per tile.
-__global__ __launch_bounds__(256) void comp_words_kernel(uint8_t* __restrict__ Xq, int ntiles, int K, int C, int nq, int R) {
+// n = nq (R + nq) > R words per tile, and the token scales.
+__global__ __launch_bounds__(256) void comp_words_kernel(uint8_t* __restrict__ Xq, float* __restrict__ xs, int64_t M,
+                                                         int ntiles, int K, int C, int nq, int R) {
   const int per = R + nq, n = nq * per;
   const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x, tile = i / n;
+  if (i < M) xs[i] = 0.0f;
   const int in = static_cast<int>(i - tile * n);
   if (tile < ntiles) *exchange_word(Xq, tile * R, K, C, in / per, in % per) = kWait;
 }
@@ -512,7 +522,8 @@ __global__ __launch_bounds__(256) void comp_words_kernel(uint8_t* __restrict__ X
 template <int RG, int C, bool GATHER, int WAVES, int PF, int KMAX>
 __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
     const uint16_t* __restrict__ X, int64_t M, int K, int64_t ldx, const int32_t* __restrict__ perm,
-    const uint16_t* __restrict__ Rt, float s_t, uint8_t* __restrict__ Xq, float* __restrict__ xs, int nq, int ntiles) {
+    const uint16_t* __restrict__ Rt, float s_t, uint8_t* __restrict__ Xq, float* __restrict__ xs, int nq, int ntiles,
+    int give_up) {
   constexpr int NT = 64 * WAVES;
   constexpr int R = 16 * RG, XS = C;
   constexpr int NBC = C / kCB, NBW = NBC / WAVES;  // blocks per chunk, per wave
@@ -698,15 +709,13 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
 #pragma unroll
     for (int w = 1; w < WAVES; ++w) m = fmaxf(m, red[w][tid]);
     red[0][tid] = m;
-    if (nq > 1)
-      __hip_atomic_store(exchange_word(Xq, row0, K, C, q, tid), __float_as_uint(m), __ATOMIC_RELAXED,
-                         __HIP_MEMORY_SCOPE_AGENT);
+    if (nq > 1) exchange_store(exchange_word(Xq, row0, K, C, q, tid), __float_as_uint(m));
   }
   if (nq > 1) {
     // Thread t < nq R waits for partner t / R's maximum of row t % R (its own
     // chunk's included).
     for (int t = tid; t < nq * R; t += NT) {
-      uint32_t v = exchange_wait(exchange_word(Xq, row0, K, C, t / R, t % R), kPollLimit);
+      uint32_t v = exchange_wait(exchange_word(Xq, row0, K, C, t / R, t % R), give_up == q);
       if (v >> 31) {
         timed_out = 1;
         v = 0;
@@ -714,8 +723,7 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
       pmax[t] = __uint_as_float(v);
     }
     __syncthreads();
-    if (tid < nq && tid != q)
-      __hip_atomic_store(exchange_word(Xq, row0, K, C, tid, R + q), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (tid < nq && tid != q) exchange_store(exchange_word(Xq, row0, K, C, tid, R + q), 0);
     if (tid < R) {
       float m = 0.0f;
       for (int p = 0; p < nq; ++p) m = fmaxf(m, pmax[p * R + tid]);
@@ -728,7 +736,11 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
     const float a_z = m * s_t;
     const float delta = a_z / 7.0f;
     gscale[tid] = delta > 0.0f ? s_t / delta : 0.0f;
-    red[1][tid] = delta / s_t;
+    const float scale = delta / s_t;
+    if (q == 0 && row0 + tid < M) {
+      if (nq == 1) xs[row0 + tid] = scale;
+      else atomicMax(reinterpret_cast<uint32_t*>(xs) + row0 + tid, __float_as_uint(scale));
+    }
   }
   __syncthreads();
 
@@ -763,11 +775,12 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
       }
   }
   if (nq > 1 && tid < nq && tid != q)  // (the other chunks have read this one's maxima)
-    if (exchange_wait(exchange_word(Xq, row0, K, C, q, R + tid), kPollLimit) >> 31) timed_out = 1;
+    if (exchange_wait(exchange_word(Xq, row0, K, C, q, R + tid), give_up == nq + q) >> 31) timed_out = 1;
   __syncthreads();
-  const bool failed = timed_out;
-  if (q == 0 && tid < R && row0 + tid < M) xs[row0 + tid] = failed ? __builtin_nanf("") : red[1][tid];
-  if (failed) return;
+  if (nq > 1 && timed_out) {
+    if (tid < R && row0 + tid < M) atomicMax(reinterpret_cast<uint32_t*>(xs) + row0 + tid, kNaN);
+    return;
+  }
   constexpr int CPR = C / 32;  // 16-byte code pieces per row of the chunk
   for (int p = tid; p < R * CPR; p += NT) {
     const int r = p / CPR, c16 = p % CPR;
@@ -779,7 +792,7 @@ __global__ __launch_bounds__(64 * WAVES) void rq_composite_x_kernel(
 
 template <int RG, int C, bool GATHER, int KMAX = C, int WAVES = 8, int PF = 2>
 int launch_composite_x(const void* X, int64_t M, int64_t K, int64_t ldx, const int32_t* perm, const void* Rt,
-                       float s, uint8_t* Xq, float* x_scale, hipStream_t stream) {
+                       float s, uint8_t* Xq, float* x_scale, hipStream_t stream, int give_up = -1) {
   constexpr int R = 16 * RG;
   const int64_t ntiles = (M + R - 1) / R;
   const int nq = static_cast<int>(K / C);
@@ -787,14 +800,14 @@ int launch_composite_x(const void* X, int64_t M, int64_t K, int64_t ldx, const i
   if (nq > 1) {
     const int64_t words = ntiles * nq * (R + nq);
     hipLaunchKernelGGL(comp_words_kernel, dim3(static_cast<unsigned>((words + 255) / 256)), dim3(256), 0, stream, Xq,
-                       static_cast<int>(ntiles), static_cast<int>(K), C, nq, R);
+                       x_scale, M, static_cast<int>(ntiles), static_cast<int>(K), C, nq, R);
     const int st = launch_status();
     if (st != OQ_OK) return st;
   }
   const int64_t grid = (ntiles + 7) / 8 * 8 * nq;
   hipLaunchKernelGGL((rq_composite_x_kernel<RG, C, GATHER, WAVES, PF, KMAX>), dim3(static_cast<unsigned>(grid)),
                      dim3(64 * WAVES), 0, stream, static_cast<const uint16_t*>(X), M, static_cast<int>(K), ldx,
-                     perm, static_cast<const uint16_t*>(Rt), s, Xq, x_scale, nq, static_cast<int>(ntiles));
+                     perm, static_cast<const uint16_t*>(Rt), s, Xq, x_scale, nq, static_cast<int>(ntiles), give_up);
   return launch_status();
 }
 
@@ -814,9 +827,9 @@ int comp_chunk(int64_t K, int cap) {
 
 int launch_composite_chunked(bool gather, int C, const void* X, int64_t M, int64_t K, int64_t ldx,
                              const int32_t* perm, const void* Rt, float s, uint8_t* Xq, float* x_scale,
-                             hipStream_t h) {
+                             hipStream_t h, int give_up = -1) {
   if (gather) {
-#define OQ_CX(CC, KM) return launch_composite_x<1, CC, true, KM>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h)
+#define OQ_CX(CC, KM) return launch_composite_x<1, CC, true, KM>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h, give_up)
     switch (C) {
       case 4096:
         if (K <= 8192) OQ_CX(4096, 8192);
@@ -829,8 +842,8 @@ int launch_composite_chunked(bool gather, int C, const void* X, int64_t M, int64
 #undef OQ_CX
   }
   switch (C) {
-    case 1024: return launch_composite_x<2, 1024, false>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
-    case 512: return launch_composite_x<2, 512, false>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
+    case 1024: return launch_composite_x<2, 1024, false>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h, give_up);
+    case 512: return launch_composite_x<2, 512, false>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h, give_up);
     default: return OQ_ERR_SHAPE;
   }
 }
@@ -934,4 +947,17 @@ extern "C" int oq_rotate_quantize_act_composite(const void* X, int64_t M, int64_
     return oq::launch_composite_chunked(true, c, X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
   if (K <= 8192) return oq::launch_composite<4, 8192>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
   return oq::launch_composite<2, 16384>(X, M, K, ldx, perm, Rt, s, Xq, x_scale, h);
+}
+
+// A call that exchanges in which one chunk gives up (see the exchange above):
+// for the tests of how a failure is reported; not part of the interface.
+extern "C" int oq_test_composite_give_up(const void* X, int64_t M, int64_t K, int64_t ldx, const int32_t* perm,
+                                         const void* Rt, uint8_t* Xq, float* x_scale, int32_t give_up, void* stream) {
+  const int c = !perm && K == 4096 ? 1024 : K > 4096 && K <= 16384 ? oq::comp_chunk(K, perm ? 4096 : 1024) : 0;
+  if (M < 1 || c == 0 || ldx < K || ldx % 8 != 0) return OQ_ERR_SHAPE;
+  if (!X || !Rt || !Xq || !x_scale) return OQ_ERR_NULL;
+  const int st = oq::device_check();
+  if (st != OQ_OK) return st;
+  return oq::launch_composite_chunked(perm != nullptr, c, X, M, K, ldx, perm, Rt, 1.0f, Xq, x_scale,
+                                      static_cast<hipStream_t>(stream), give_up);
 }

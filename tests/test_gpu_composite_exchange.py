@@ -1,12 +1,14 @@
 """The exchange of row maxima between the chunks of a composite rotation (GPU): calls on
 several streams at once, and captured calls that are replayed, give what a call alone
 gives; every form that exchanges (online permutation and folded, each chunk width, a
-partial last tile)."""
-import numpy as np
+partial last tile); and a chunk that gives up a wait always shows in the token scales."""
+import ctypes as C
+
 import pytest
 import torch
 
 import paper_2605_28803_amd as oq
+from paper_2605_28803_amd import _lib
 
 pytestmark = pytest.mark.gpu
 DEV = torch.device("cuda:0")
@@ -68,3 +70,29 @@ def test_captured_calls(K, folded):
         q, s = oq.rotate_quantize_act_composite(src, perm, Rt)
         torch.cuda.synchronize()
         assert torch.equal(Xq, q) and torch.equal(xs, s)
+
+
+@pytest.mark.parametrize("K,folded,chunks", [(16384, False, 4), (5120, False, 5), (4608, True, 9), (4096, True, 4)])
+def test_a_chunk_that_gives_up_shows_in_the_scales(K, folded, chunks):
+    """Each chunk in turn gives up its wait for the maxima, then its wait for the acknowledgements: no token scale is a
+    number, and nothing past the outputs is written.  A call with no such chunk gives the ordinary result."""
+    M = 1031
+    X, perm, Rt = _inputs(M, K, folded, 1.0)
+    f = _lib.load().oq_test_composite_give_up
+    f.argtypes = [C.c_void_p, C.c_int64, C.c_int64, C.c_int64, C.c_void_p, C.c_void_p, C.c_void_p, C.c_void_p, C.c_int32,
+                  C.c_void_p]
+    f.restype = C.c_int
+    ref, rs = oq.rotate_quantize_act_composite(X, perm, Rt)
+    for chunk in [-1] + list(range(2 * chunks)):
+        print(f"give up K={K} folded={folded} chunk={chunk}", flush=True)
+        Xq = torch.zeros((M + 1, K // 2), dtype=torch.uint8, device=DEV)
+        xs = torch.full((M + 1,), 5.0, device=DEV)
+        st = f(X.data_ptr(), M, K, K, None if perm is None else perm.data_ptr(), Rt.data_ptr(), Xq.data_ptr(),
+               xs.data_ptr(), chunk, torch.cuda.current_stream().cuda_stream)
+        assert st == 0
+        torch.cuda.synchronize()
+        if chunk < 0:
+            assert torch.equal(Xq[:M], ref) and torch.equal(xs[:M], rs)
+        else:
+            assert torch.isnan(xs[:M]).all()
+        assert not Xq[M].any() and xs[M].item() == 5.0
