@@ -61,4 +61,37 @@ constexpr SmallShape small_shape(int64_t N, int64_t K, bool a8) {
   return {1, K <= 1024 ? 4 : 16, K < 128 ? 0 : K <= 1024 ? 2 : K <= 2048 || a8 ? 1 : 2};
 }
 
+// The ring's tilings.  Estimated time of one: fixed + (rounds - 1) * 2 us + K *
+// (one tile on a CU: lat; n tiles sharing a CU: n * thr).  The constants are
+// fitted to measured times (ns per code of K and tile, us) of every tiling at
+// ten shapes from 128 x 4096 x 4096 to 16384 x 8192 x 8192, which they reproduce
+// within about 10%; occ: workgroups per CU.
+struct RingCost {
+  int bm, bn, occ;
+  float lat, thr, fixed;
+};
+constexpr RingCost kRingCost[] = {{256, 256, 1, 12.5f, 11.9f, 8.0f},  // 8 waves of 128 x 64, 256-code stages
+                                  {128, 128, 2, 3.4f, 3.35f, 4.6f},   // 4 waves of 64 x 64
+                                  {128, 64, 3, 2.45f, 1.92f, 3.9f},   // 4 waves of 64 x 32
+                                  {64, 64, 2, 0.9f, 1.0f, 5.4f},      // 4 K groups of 2 waves of 64 x 32, 512-code stages
+                                  {64, 64, 2, 1.45f, 1.15f, 3.7f}};   // 4 waves of 32 x 32, 512-code stages
+constexpr RingCost kRingCostA8[] = {{256, 256, 1, 14.2f, 14.3f, 8.0f},   // 8 waves of 128 x 64, 128-code stages
+                                    {128, 128, 2, 5.1f, 4.35f, 4.5f},    // 4 waves of 64 x 64
+                                    {64, 64, 2, 2.2f, 1.6f, 4.4f}};      // 2 K groups of 2 waves of 64 x 32
+constexpr float ring_estimate(const RingCost& c, int64_t M, int64_t N, int64_t K) {
+  const int64_t tiles = ((M + c.bm - 1) / c.bm) * ((N + c.bn - 1) / c.bn);
+  const int64_t n = (tiles + 255) / 256, rounds = (n + c.occ - 1) / c.occ;
+  const float k = 1e-3f * static_cast<float>(K);
+  return c.fixed + 2.0f * static_cast<float>(rounds - 1) + k * (n == 1 ? c.lat : static_cast<float>(n) * c.thr);
+}
+// Index of the tiling with the lowest estimate.
+constexpr int ring_tiling(int64_t M, int64_t N, int64_t K, bool a8) {
+  const RingCost* c = a8 ? kRingCostA8 : kRingCost;
+  const int count = a8 ? 3 : 5;
+  int best = 0;
+  for (int i = 1; i < count; ++i)
+    if (ring_estimate(c[i], M, N, K) < ring_estimate(c[best], M, N, K)) best = i;
+  return best;
+}
+
 }  // namespace oq

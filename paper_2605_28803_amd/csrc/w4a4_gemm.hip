@@ -352,29 +352,6 @@ int launch_ring(const GemmArgs& a, Epilogue epi, hipStream_t stream) {
   return launch_status();
 }
 
-// Estimated time of a tiling: fixed + (rounds - 1) * 2 us + K * (one tile on a
-// CU: lat; n tiles sharing a CU: n * thr).  The constants are fitted to
-// measured times (ns per code of K and tile, us) of every tiling at ten shapes
-// from 128 x 4096 x 4096 to 16384 x 8192 x 8192, which they reproduce within
-// about 10%; occ: workgroups per CU.
-struct RingCost {
-  int bm, bn, occ;
-  float lat, thr, fixed;
-};
-float ring_estimate(const RingCost& c, const GemmArgs& a) {
-  const int64_t tiles = ((a.M + c.bm - 1) / c.bm) * ((a.N + c.bn - 1) / c.bn);
-  const int64_t n = (tiles + 255) / 256, rounds = (n + c.occ - 1) / c.occ;
-  const float k = 1e-3f * static_cast<float>(a.K);
-  return c.fixed + 2.0f * static_cast<float>(rounds - 1) + k * (n == 1 ? c.lat : static_cast<float>(n) * c.thr);
-}
-template <int NT>
-int ring_best(const RingCost (&c)[NT], const GemmArgs& a) {
-  int best = 0;
-  for (int i = 1; i < NT; ++i)
-    if (ring_estimate(c[i], a) < ring_estimate(c[best], a)) best = i;
-  return best;
-}
-
 int gemm_launch(const GemmArgs& a, Epilogue epi, hipStream_t stream) {
   if (a.M == 0) return OQ_OK;
   if (a.a_i8 && (epi == EPI_RESID_F32 || epi == EPI_GELU_F16)) return OQ_ERR_ARG;
@@ -389,21 +366,13 @@ int gemm_launch(const GemmArgs& a, Epilogue epi, hipStream_t stream) {
     }
   }
   if (a.a_i8) {
-    static const RingCost cost8[] = {{256, 256, 1, 14.2f, 14.3f, 8.0f},   // 8 waves of 128 x 64, 128-code stages
-                                     {128, 128, 2, 5.1f, 4.35f, 4.5f},    // 4 waves of 64 x 64
-                                     {64, 64, 2, 2.2f, 1.6f, 4.4f}};      // 2 K groups of 2 waves of 64 x 32
-    switch (ring_best(cost8, a)) {
+    switch (ring_tiling(a.M, a.N, a.K, true)) {
       case 0: return launch_ring<2, 4, 4, 2, true, 4, 3, 1, 2>(a, epi, stream);
       case 1: return launch_ring<2, 2, 2, 2, true, 4, 3, 1, 1>(a, epi, stream);
       default: return launch_ring<1, 2, 2, 1, true, 8, 2, 2, 1>(a, epi, stream);
     }
   }
-  static const RingCost cost[] = {{256, 256, 1, 12.5f, 11.9f, 8.0f},  // 8 waves of 128 x 64, 256-code stages
-                                  {128, 128, 2, 3.4f, 3.35f, 4.6f},   // 4 waves of 64 x 64
-                                  {128, 64, 3, 2.45f, 1.92f, 3.9f},   // 4 waves of 64 x 32
-                                  {64, 64, 2, 0.9f, 1.0f, 5.4f},      // 4 K groups of 2 waves of 64 x 32, 512-code stages
-                                  {64, 64, 2, 1.45f, 1.15f, 3.7f}};   // 4 waves of 32 x 32, 512-code stages
-  switch (ring_best(cost, a)) {
+  switch (ring_tiling(a.M, a.N, a.K, false)) {
     case 0: return launch_ring<2, 4, 4, 2, false, 8, 2, 1, 4>(a, epi, stream);
     case 1: return launch_ring<2, 2, 2, 2, false, 8, 2, 1, 1>(a, epi, stream);
     case 2: return launch_ring<2, 2, 2, 1, false, 8, 2, 1, 1>(a, epi, stream);

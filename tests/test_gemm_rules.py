@@ -6,11 +6,14 @@ import subprocess
 
 import pytest
 
+from tests import test_gpu_gemm_tiles as tiles
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_2605_28803_amd", "csrc")
 
 SOURCE = r"""
 #include "gemm_rules.h"
+extern "C" int ring_tiling(int64_t M, int64_t N, int64_t K, bool a8) { return oq::ring_tiling(M, N, K, a8); }
 extern "C" bool few_rows(int64_t M, int64_t N, int64_t K, bool a8, bool tiled) { return oq::few_rows(M, N, K, a8, tiled); }
 extern "C" void small_shape(int64_t N, int64_t K, bool a8, int* out) {
   const oq::SmallShape s = oq::small_shape(N, K, a8);
@@ -29,6 +32,7 @@ def rules(tmp_path_factory):
     lib.small_shape.argtypes = [C.c_int64, C.c_int64, C.c_bool, C.POINTER(C.c_int)]
     lib.few_rows.argtypes = [C.c_int64] * 3 + [C.c_bool] * 2
     lib.few_rows.restype = C.c_bool
+    lib.ring_tiling.argtypes = [C.c_int64] * 3 + [C.c_bool]
     return lib
 
 
@@ -80,3 +84,36 @@ def test_few_row_rule_takes_what_only_the_small_kernel_reads(rules):
             for K in (128, 1024, 16384):
                 assert rules.few_rows(M, N, K, False, True)
                 assert rules.few_rows(M, N, K, False, False) <= (M <= 64)
+
+
+# Ring tilings by index: W4A4 256 x 256, 128 x 128, 128 x 64, 64 x 64 with four K groups, 64 x 64; W4A8 256 x 256, 128 x 128,
+# 64 x 64 with two K groups.  What the GPU tests' shapes say beside them.
+TILING = {"W4A4": [0, 0, 1, 1, 2, 2, 3, 3, 3, 4, 4, 4, 4], "W4A8": [0, 1, 1, 2, 2, 2]}
+
+
+@pytest.mark.parametrize("name", sorted(TILING))
+def test_tiling_shapes_take_the_tiling_they_name(rules, name):
+    shapes = getattr(tiles, name)
+    assert len(shapes) == len(TILING[name])
+    for (M, N, K), tiling in zip(shapes, TILING[name]):
+        assert not rules.few_rows(M, N, K, name == "W4A8", False)
+        assert rules.ring_tiling(M, N, K, name == "W4A8") == tiling, (M, N, K)
+
+
+def test_few_row_shapes_take_the_kernel_they_name(rules):
+    on_ring = {(17, 8200, 1088): (4, 2), (64, 8200, 4160): (3, 2)}  # (W4A4, W4A8) tilings
+    for M, N, K in tiles.FEW:
+        for a8 in (False, True):
+            assert rules.few_rows(M, N, K, a8, False) == ((M, N, K) not in on_ring)
+            if (M, N, K) in on_ring:
+                assert rules.ring_tiling(M, N, K, a8) == on_ring[M, N, K][a8]
+
+
+def test_residual_linears_take_the_tiling_they_name(rules):
+    cfg = tiles.RESID["gr00t_2000"][0]
+    rows, d, f = cfg.batch * cfg.tokens, cfg.hidden, cfg.mlp
+    assert (rows, d, f) == (2000, 1536, 6144)
+    assert [rules.ring_tiling(rows, n, k, False) for n, k in ((d, d), (d, f), (f, d))] == [2, 1, 1]  # o, ff2, ff0
+    cfg = tiles.RESID["pi_8192"][0]
+    rows, d, f = cfg.batch * cfg.tokens, cfg.hidden, cfg.mlp
+    assert [rules.ring_tiling(rows, n, k, False) for n, k in ((d, d), (2 * f, d), (d, f))] == [0, 0, 0]  # o, gate|up, down

@@ -1,10 +1,11 @@
 """Every tiling of the M > 64 product at its edges (GPU).
 
 The launcher picks one of five W4A4 and three W4A8 tilings from an estimate
-of their times; each shape below takes the one named beside it, with rows and
-columns that are not a multiple of its tile, a last K stage that is partly
-empty (K % 64 == 0 is all that is asked), a single stage, and in the deep
-cases every K group ending on a short stage.  int32 accumulators are exact;
+of their times; each shape below takes the one named beside it (test_gemm_rules
+asks the launcher's rule, on the host), with rows and columns that are not a
+multiple of its tile, a last K stage that is partly empty (K % 64 == 0 is all
+that is asked), a single stage, and in the deep cases every K group ending on a
+short stage.  int32 accumulators are exact;
 fp16 / bf16 outputs are one rounding of an fp32 value (2^-11, 2^-8 of the
 value, plus the fp32 epilogue's few ulp), against the float64 oracle.  The
 residual outputs of the same tilings run through a DiT block (oracle on the
