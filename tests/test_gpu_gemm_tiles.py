@@ -39,7 +39,7 @@ W4A4 = [
 # both widths), and a 20-row product of more than 8192 columns that stays on it (K = 576).
 FEW = [(16, 8256, 1088), (17, 8192, 1088), (17, 8200, 1088), (64, 8200, 4160), (1, 16384, 8256), (16, 16392, 8192),
        (5, 4100, 2048), (5, 4096, 2048), (16, 4100, 2112), (3, 2560, 2112), (5, 5000, 1984), (40, 5000, 1984),
-       (1, 100, 64), (50, 4100, 64), (20, 8232, 576)]
+       (1, 104, 64), (2, 100, 64), (50, 4100, 64), (20, 8232, 576)]
 W4A8 = [
     (4000, 4092, 4160),                    # 256 x 256; half a 128-code stage
     (1000, 6100, 1600), (816, 2560, 2112),  # 128 x 128
