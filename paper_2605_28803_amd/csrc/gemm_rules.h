@@ -84,12 +84,24 @@ constexpr float ring_estimate(const RingCost& c, int64_t M, int64_t N, int64_t K
   const float k = 1e-3f * static_cast<float>(K);
   return c.fixed + 2.0f * static_cast<float>(rounds - 1) + k * (n == 1 ? c.lat : static_cast<float>(n) * c.thr);
 }
-// Index of the tiling with the lowest estimate.
+// Index of the tiling.  K <= 256, W4A4: 5 or 6, 64 x 64 and 128 x 64 tiles of 4
+// waves with 128-code stages.  There a tile is one or two stages; the others'
+// 256- and 512-code stages load and multiply what is not there, and their two
+// buffers leave room for fewer workgroups a CU, while such a product is bound by
+// its output stores, which want many in flight.  64 x 64 as long as a CU gets three
+// of them, us against the best of the others: 65 x 16384 x 128 5.5 -> 4.2,
+// 600 x 4096 x 128 5.8 -> 4.8;
+// above, 128 x 64: 4080 x 4096 x 64 14.0 -> 11.7, 8192 x 8192 x 256 44.4 -> 37.0.
+// W4A8 up to K = 256: no 256 x 256 tiles while a CU gets at most five of them, for
+// the same reason: 1100 x 32768 x 128 32.1 us, with 128 x 128 25.8; 2500 x 32768 x 256 60.6 / 56.3; but
+// 4080 x 32768 x 128 90.5 / 102.
+// Else the one with the lowest estimate.
 constexpr int ring_tiling(int64_t M, int64_t N, int64_t K, bool a8) {
+  if (!a8 && K <= 256) return ((M + 63) / 64) * ((N + 63) / 64) <= 768 ? 5 : 6;
   const RingCost* c = a8 ? kRingCostA8 : kRingCost;
   const int count = a8 ? 3 : 5;
-  int best = 0;
-  for (int i = 1; i < count; ++i)
+  int best = a8 && K <= 256 && ((M + 255) / 256) * ((N + 255) / 256) <= 1280 ? 1 : 0;
+  for (int i = best + 1; i < count; ++i)
     if (ring_estimate(c[i], M, N, K) < ring_estimate(c[best], M, N, K)) best = i;
   return best;
 }

@@ -377,7 +377,9 @@ int gemm_launch(const GemmArgs& a, Epilogue epi, hipStream_t stream) {
     case 1: return launch_ring<2, 2, 2, 2, false, 8, 2, 1, 1>(a, epi, stream);
     case 2: return launch_ring<2, 2, 2, 1, false, 8, 2, 1, 1>(a, epi, stream);
     case 3: return launch_ring<1, 2, 2, 1, false, 16, 2, 4, 1>(a, epi, stream);
-    default: return launch_ring<2, 2, 1, 1, false, 16, 2, 1, 1>(a, epi, stream);
+    case 4: return launch_ring<2, 2, 1, 1, false, 16, 2, 1, 1>(a, epi, stream);
+    case 5: return launch_ring<2, 2, 1, 1, false, 4, 2, 1, 1>(a, epi, stream);
+    default: return launch_ring<2, 2, 2, 1, false, 4, 2, 1, 1>(a, epi, stream);
   }
 }
 

@@ -86,9 +86,9 @@ def test_few_row_rule_takes_what_only_the_small_kernel_reads(rules):
                 assert rules.few_rows(M, N, K, False, False) <= (M <= 64)
 
 
-# Ring tilings by index: W4A4 256 x 256, 128 x 128, 128 x 64, 64 x 64 with four K groups, 64 x 64; W4A8 256 x 256, 128 x 128,
-# 64 x 64 with two K groups.  What the GPU tests' shapes say beside them.
-TILING = {"W4A4": [0, 0, 1, 1, 2, 2, 3, 3, 3, 4, 4, 4, 4], "W4A8": [0, 1, 1, 2, 2, 2]}
+# Ring tilings by index: W4A4 256 x 256, 128 x 128, 128 x 64, 64 x 64 with four K groups, 64 x 64, and with 128-code stages 64 x
+# 64 and 128 x 64; W4A8 256 x 256, 128 x 128, 64 x 64 with two K groups.  What the GPU tests' shapes say beside them.
+TILING = {"W4A4": [0, 0, 1, 1, 2, 2, 3, 3, 3, 4, 4, 5, 5, 5, 6, 6], "W4A8": [0, 1, 1, 2, 2, 2, 1]}
 
 
 @pytest.mark.parametrize("name", sorted(TILING))
@@ -98,6 +98,22 @@ def test_tiling_shapes_take_the_tiling_they_name(rules, name):
     for (M, N, K), tiling in zip(shapes, TILING[name]):
         assert not rules.few_rows(M, N, K, name == "W4A8", False)
         assert rules.ring_tiling(M, N, K, name == "W4A8") == tiling, (M, N, K)
+
+
+# (M, N, K, us with each of the seven W4A4 tilings): short K.
+SHORT = [(65, 16384, 128, 9.84, 5.91, 5.06, 6.21, 5.57, 4.23, 4.59), (600, 4096, 128, 10.48, 6.26, 5.78, 8.27, 7.63, 4.83, 5.18),
+         (4080, 4096, 64, 14.03, 14.77, 15.21, 30.48, 28.80, 12.46, 11.88), (8192, 8192, 256, 48.54, 44.19, 44.93, 110.94, 100.90, 41.17, 37.02)]
+
+
+@pytest.mark.parametrize("shape", SHORT)
+def test_short_k_takes_the_fastest_tiling(rules, shape):
+    M, N, K, *us = shape
+    assert rules.ring_tiling(M, N, K, False) == us.index(min(us))
+
+
+def test_short_k_of_w4a8_takes_128x128(rules):
+    assert rules.ring_tiling(1100, 32768, 128, True) == 1 and rules.ring_tiling(2500, 16384, 192, True) == 1
+    assert rules.ring_tiling(4080, 32768, 128, True) == 0  # (90.5 us, 128 x 128 102)
 
 
 def test_few_row_shapes_take_the_kernel_they_name(rules):
@@ -117,3 +133,6 @@ def test_residual_linears_take_the_tiling_they_name(rules):
     cfg = tiles.RESID["pi_8192"][0]
     rows, d, f = cfg.batch * cfg.tokens, cfg.hidden, cfg.mlp
     assert [rules.ring_tiling(rows, n, k, False) for n, k in ((d, d), (2 * f, d), (d, f))] == [0, 0, 0]  # o, gate|up, down
+    for name, tiling in (("gr00t_narrow", 5), ("gr00t_narrow_801", 6)):
+        cfg = tiles.RESID[name][0]
+        assert rules.ring_tiling(cfg.batch * cfg.tokens, cfg.hidden, cfg.mlp, False) == tiling and cfg.hidden == cfg.mlp

@@ -1,6 +1,6 @@
 """Every tiling of the M > 64 product at its edges (GPU).
 
-The launcher picks one of five W4A4 and three W4A8 tilings from an estimate
+The launcher picks one of seven W4A4 and three W4A8 tilings from an estimate
 of their times; each shape below takes the one named beside it (test_gemm_rules
 asks the launcher's rule, on the host), with rows and columns that are not a
 multiple of its tile, a last K stage that is partly empty (K % 64 == 0 is all
@@ -32,7 +32,9 @@ W4A4 = [
     (1000, 6100, 1600), (1100, 8200, 1344),  # 128 x 64; 64 codes
     (520, 1000, 6208), (130, 4100, 4160),  # 64 x 64, four K groups; 64 codes in the last 512-code stage
     (992, 1536, 6528),                     # 64 x 64, four K groups; 384 codes
-    (70, 100, 64), (65, 100, 192), (1000, 1544, 576), (300, 520, 320),  # 64 x 64; a single short stage, tails
+    (1000, 1544, 576), (300, 520, 320),    # 64 x 64; tails
+    (70, 100, 64), (65, 100, 192), (1000, 2500, 256),  # 64 x 64, 128-code stages; one half full, one and a half, two
+    (1000, 4100, 64), (3010, 2052, 192),   # 128 x 64, 128-code stages
 ]
 # Few rows: 16 | 17 and 8192 | 8193 columns (the small-M kernel and the 64 x 64 tilings), one row block deep and wide, and
 # the small-M kernel's rounds of no whole unit (K = 64), one, two and more units per wave (K = 2048 and its neighbours,
@@ -44,6 +46,7 @@ W4A8 = [
     (4000, 4092, 4160),                    # 256 x 256; half a 128-code stage
     (1000, 6100, 1600), (816, 2560, 2112),  # 128 x 128
     (70, 100, 64), (300, 520, 320), (1000, 1544, 576),  # 64 x 64, two K groups
+    (1000, 9000, 192),                     # 128 x 128; short K
 ]
 
 
@@ -95,11 +98,16 @@ def test_w4a8_tilings(M, N, K):
 
 
 # Residual (and GELU) outputs: o and ff2 of 2000 rows take the 128 x 64 and 128 x 128
-# tilings, ff0 the 128 x 128 one; 8192 rows of a 2048-wide model the 256 x 256 one.
+# tilings, ff0 the 128 x 128 one; 8192 rows of a 2048-wide model the 256 x 256 one;
+# a 256-wide model the two of short K (1008 rows 64 x 64, 12816 rows 128 x 64).
 RESID = {
     "gr00t_2000": (dataclasses.replace(configs.DIT_GR00T, name="gr00t_2000", n_blocks=2, batch=125, prefix=20), (0, 1)),
     "pi_8192": (dataclasses.replace(configs.DIT_PI, name="pi_8192", n_blocks=1, batch=128, tokens=64, hidden=2048,
                                     mlp=2048, n_heads=16, head_dim=128, prefix=16, steps=2), (0,)),
+    "gr00t_narrow": (dataclasses.replace(configs.DIT_GR00T, name="gr00t_narrow", n_blocks=1, batch=63, hidden=256, mlp=256,
+                                         n_heads=4, head_dim=64, prefix=5, steps=2), (0,)),
+    "gr00t_narrow_801": (dataclasses.replace(configs.DIT_GR00T, name="gr00t_narrow_801", n_blocks=1, batch=801, hidden=256,
+                                             mlp=256, n_heads=4, head_dim=64, prefix=5, steps=2), (0,)),
 }
 
 
