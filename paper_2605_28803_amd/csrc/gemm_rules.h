@@ -22,24 +22,44 @@ namespace oq {
 // Between 8192 and 16384 columns the ring has at most one 64 x 64 tile per CU,
 // so its time is a tile's whole K, and with few rows the small-M kernel stays
 // ahead where its own K loop is short or the ring's long:
+//  * K = 64, one step on either: 17 x 8200 x 64 2.8 / 3.1, 48 x 9000 x 64 3.4 / 3.4, 64 x
+//    9000 x 64 3.7 / 3.4; W4A8, whose ring has no short stages, 64 x 9000 x 64 3.8 / 4.2.
 //  * up to K = 1024, where a wave loads all it needs at once (above, it takes a
-//    second round).  The ring's stages are 512 codes (8-bit tokens: 256), so it
-//    is ahead at a whole number of them: 32 x 8200 x 576 4.1 / 5.1, x 1024 4.6 / 5.1, 48 x
-//    12288 x 576 4.8 / 5.4, x 1024 5.9 / 5.6; W4A8 24 x 12288 x 576 5.2 / 5.5, x 768 5.9 / 5.5,
-//    17 x 8200 x 1024 5.1 / 5.9, 28 x 9000 x 1024 6.2 / 6.0.
+//    second round).  The ring's stages are 512 codes (up to K = 256: 128; 8-bit
+//    tokens: 256), so it is ahead at a whole number of them: W4A4 17 x 8200 x 128 3.4 / 3.3,
+//    x 192 3.5 / 3.6, x 384 3.6 / 4.1, x 512 4.0 / 4.3 but 32 x 8200 x 512 4.5 / 4.3, 40 x 12288 x 448 4.3 / 4.4,
+//    64 x 8200 x 640 4.3 / 5.2, 64 x 16384 x 896 5.9 / 6.2, 64 x 9000 x 832 6.0 / 5.8, 40 x 12288 x 1024 5.7 / 5.7, 48 x
+//    9000 x 1024 5.7 / 5.5; W4A8 24 x 8200 x 320 4.6 / 4.3, 40 x 8200 x 576 4.9 / 5.0, 24 x 12288 x
+//    576 5.2 / 5.5, x 768 5.9 / 5.5, 24 x 8200 x 640 4.9 / 4.7, 48 x 16384 x 832 6.7 / 6.8, 24 x
+//    9000 x 896 5.3 / 5.2, 17 x 8200 x 1024 5.1 / 5.9, 28 x 9000 x 1024 6.2 / 6.0.
+//    A second tile for some CUs leaves that so up to 24576 columns, for fewer rows:
+//    W4A4 48 x 20000 x 640 6.7 / 7.1, 17 x 20000 x 704 6.5 / 6.8, 17 x 16392 x 1024 5.9 / 6.3, but
+//    17 x 32768 x 640 7.3 / 7.1.
 //  * deep K of W4A8, whose tile takes twice the LDS reads: 17 x 8200 x 8192 25.9 /
 //    28.6, 17 x 8200 x 16384 43.4 / 53.3, 28 x 8200 x 16384 49.9 / 53.6, 17 x 16384 x 16384 53.5 /
 //    58.1; but 24 x 9000 x 8192 30.6 / 28.9, 24 x 10000 x 16384 54.8 / 53.6.
 constexpr bool few_rows(int64_t M, int64_t N, int64_t K, bool a8, bool tiled) {
   if (tiled || M <= 16) return true;
-  if (M > 64 || N > 16384) return false;
+  if (M > 64) return false;
   if (N <= 8192) return true;
+  if (N > 16384) {
+    if (a8 || N > 24576 || K <= 512 || K > 1024) return false;
+    return M <= (K % 256 == 128 ? 48 : K % 256 ? 32 : 20);
+  }
+  if (K == 64) return a8 || M <= 48;
   if (a8) {
-    if (K > 512 && K < 768) return M <= 48;
-    if (K > 768 && K <= 1024) return M <= 24;
+    if (K == 576 || K == 704) return M <= (N < 9000 ? 40 : 24);
+    if (K == 640 || K == 768) return N < 9000 && M <= 20;
+    if (K == 832 || K == 960) return N < 9000 || M <= 48;
+    if (K == 896 || K == 1024) return M <= (N < 9000 ? 40 : 24);
     return (K >= 4096 && N < 9000 && M <= (K > 8192 ? 28 : 24)) || (K > 8192 && M <= 20);
   }
-  return K > 512 && K <= 1024 && M <= (K < 768 || N < 9000 ? 48 : 36);
+  if (K == 192) return N < 9000 && M <= 32;
+  if (K <= 256 || K > 1024) return false;
+  if (K < 512) return N < 9000 || M <= 40;
+  if (K == 512) return N < 9000 && M <= 24;
+  if (K % 256 == 0) return M <= (N < 9000 ? 48 : 40);
+  return K < 768 || K == 896 || N < 9000 || M <= 56;
 }
 
 // Shape of the small-M (weight-streaming) product: 16 nb columns a workgroup

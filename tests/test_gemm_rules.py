@@ -70,6 +70,17 @@ MEASURED = [
     (24, 8200, 8192, True, 27.6, 28.7), (28, 8200, 16384, True, 49.9, 53.6), (24, 9000, 8192, True, 30.6, 28.9),
     (24, 10000, 16384, True, 54.8, 53.6), (17, 20000, 16384, True, 76.0, 59.4), (40, 32768, 2048, True, 25.0, 12.8),
     (64, 32768, 8192, True, 92.7, 41.3),
+    (17, 8200, 64, False, 2.82, 3.13), (48, 9000, 64, False, 3.38, 3.43), (64, 9000, 64, False, 3.70, 3.43),
+    (17, 20000, 64, False, 4.31, 3.66), (64, 9000, 64, True, 3.75, 4.16), (64, 16392, 64, True, 5.13, 4.57),
+    (17, 9000, 128, False, 3.87, 3.44), (24, 8200, 192, False, 3.52, 3.62), (17, 9000, 192, False, 3.77, 3.60),
+    (64, 8200, 256, False, 5.23, 3.77), (17, 8200, 384, False, 3.62, 4.12),
+    (40, 12288, 448, False, 4.28, 4.38), (64, 9000, 448, False, 4.80, 4.44), (32, 8200, 512, False, 4.45, 4.32),
+    (64, 8200, 640, False, 4.33, 5.21), (64, 16384, 896, False, 5.91, 6.21), (64, 9000, 832, False, 6.04, 5.79),
+    (56, 9000, 704, False, 4.97, 5.27), (48, 20000, 640, False, 6.65, 7.11),
+    (56, 20000, 704, False, 7.83, 7.43), (17, 16392, 1024, False, 6.00, 6.51), (17, 32768, 640, False, 7.29, 7.08),
+    (24, 8200, 320, True, 4.59, 4.26), (17, 8200, 576, True, 4.36, 4.72), (24, 9000, 640, True, 5.17, 4.73),
+    (17, 8200, 768, True, 5.03, 5.28), (64, 9000, 832, True, 6.21, 5.72), (17, 16384, 960, True, 5.58, 6.18),
+    (40, 9000, 896, True, 6.09, 5.48),
 ]
 
 
