@@ -848,9 +848,11 @@ int launch_composite_chunked(bool gather, int C, const void* X, int64_t M, int64
   }
 }
 
-// Rows that one chunk holds (K = 512 n up to 4096): the chunked kernel with nq =
-// 1, without exchange or workspace.  *st is set and true returned if K is one of
-// the widths built.  (Against rq_composite1_kernel, which stays for the other K
+// Rows that one chunk holds: the chunked kernel with nq = 1, without exchange.
+// *st is set and true returned if K is one of the widths built (512, 1024, 1536,
+// 2048, 3072, 4096).  2560 and 3584 would fit the kernel too; no instance is built
+// for them, so they take rq_composite1_kernel (4080 rows: 26 and 30 us with the
+// permutation).  (Against rq_composite1_kernel, which stays for the other K
 // up to 4096: 4080 x 2048 22 -> 11 us, 16384 x 1024 23 -> 18 us, 700 x 4096 28 ->
 // 16 us; with P folded 22 -> 9, 25 -> 12, 28 -> 11 us.)
 bool launch_composite_one(bool gather, const void* X, int64_t M, int64_t K, int64_t ldx, const int32_t* perm,

@@ -16,7 +16,7 @@
 // so the dot products are unchanged.
 //
 // Two kernels.  M > 64 (and fewer rows of wide products): LDS-staged tiles on
-// v_mfma_i32_32x32x32_i8 (gemm_ring.h; the tile by the estimate in gemm_launch).
+// v_mfma_i32_32x32x32_i8 (gemm_ring.h; kernel and tile by the rules of gemm_rules.h).
 // Other M <= 64 (and token codes in the 16-row tiled layout): a weight-streaming kernel on
 // v_mfma_i32_16x16x64_i8 with the operands loaded straight into registers
 // (details at gemm_small_kernel).  8-bit token codes (W4A8) use both with

@@ -1,8 +1,8 @@
 """The composite rotation's chunk widths at their edges (GPU).
 
-Every width that holds a whole row (512 n up to 4096, with 16- and, folded and
-with more than 1024 rows, 32-row tiles), the widths next to them that take the
-other kernels, and every chunk width above 4096 with its raw-row sizes, at one
+Every width built that holds a whole row (512, 1024, 1536, 2048, 3072 and 4096,
+with 16- and, folded and with more than 1024 rows, 32-row tiles), other widths,
+which take the other kernels, and every chunk width above 4096 with its raw-row sizes, at one
 row, one row short of and past a tile, and past the 1024-row rule: codes by the
 boundary rule of the oracle fed the same block matrices, token scales within the
 same bound."""
@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
 
 CASES = [(1, 512), (17, 512), (1040, 512), (15, 1024), (33, 1024), (1025, 1024), (31, 1536), (17, 2048), (47, 2048),
          (1, 3072), (17, 3072), (1, 4096), (47, 4096), (1025, 4096),
-         (17, 448), (17, 576), (17, 2560),                                    # not a width of its own
+         (17, 448), (17, 576), (17, 2560), (17, 3584),                        # no instance of their own
          (1, 8192), (31, 8192), (17, 12288), (17, 10240), (33, 9216), (17, 8704), (15, 16384)]
 
 
