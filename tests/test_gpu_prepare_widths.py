@@ -1,8 +1,8 @@
 """The weight preparation at the widths where its kernels change (GPU): the channel
 energies' column split (16, 32 and 64 columns a workgroup: K below and at 2048 and 6144),
 with ragged columns and row counts around a round of a workgroup's rows, and the Gram
-matrices' split (six workgroups a block up to K = 2048, one above); and the
-precision of a single Jacobi rotation."""
+matrices' split (six workgroups a block up to K = 2048, one above); the zigzag's split of
+its count; and the precision of a single Jacobi rotation."""
 import numpy as np
 import pytest
 import torch
@@ -30,6 +30,18 @@ def test_channel_energy_column_split(N, K):
     ref = composite.channel_energy(w16.astype(np.float64))
     assert np.all(np.abs(e - ref) <= 2 * N * EPS * ref)
     assert np.all(e[[1, 15, 16, 31, 63, 64, K - 1]] == e[0])
+
+
+@pytest.mark.parametrize("K,block", [(64, 64), (36, 4), (15 * 4, 4), (16 * 64, 64), (2048, 64), (2052, 4), (2112, 64),
+                                     (4096 + 192, 64)])
+def test_zigzag_count_split(K, block):
+    """The 16 waves' shares of up to 2048 energies, whole and uneven, with few distinct values (ties go to the lower
+    index): equal to the oracle."""
+    print(f"zigzag K={K} block={block}", flush=True)
+    rng = np.random.default_rng(6600 + K)
+    for e in (rng.integers(0, 7, K).astype(np.float64), np.zeros(K), rng.standard_normal(K) ** 2):
+        perm = oq.zigzag_permutation(torch.from_numpy(e).to(DEV), block).cpu().numpy()
+        assert np.array_equal(perm, composite.zigzag_permutation(e, K // block))
 
 
 @pytest.mark.parametrize("N,K", [(1, 2048), (257, 2048), (1, 2112), (63, 2112), (65, 3072), (1025, 4096)])
